@@ -380,7 +380,9 @@ int reflex_moe_forward_noalloc(const reflex_moe_args* args, void* stream);
  *   launch computes the counts and the scores as d/256 partial sums, which step 3 adds
  *   with the bias), 2 counts done (budget / rule / uniform fill / reuse),
  *   3 count scan + TopK done, 4 permutation + GEMM tile plan done,
- *   5 gate/up GEMM done, 6 down GEMM done, 7 shared expert done, 8 combine done.
+ *   5 gate/up GEMM done, 6 down GEMM done, 7 shared expert done (nothing is left to do
+ *   there where its rows ride in the two GEMMs: f_shared = f and T * kcap <= 5 E),
+ *   8 combine done.
  * stage_events: host array of REFLEX_N_STAGE_EVENTS hipEvent_t handles created by
  * the caller (hipEventCreate); the library only records them.
  * Errors: as reflex_moe_forward; NULL stage_events or a NULL entry;

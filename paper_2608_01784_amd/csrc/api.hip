@@ -195,6 +195,16 @@ struct Layout {
       pair_to_sorted, perm, route_hist, swiglu, y, shared_act, shared_y, total;
 };
 
+// An always-on expert as wide as the routed ones rides in their two GEMM launches (its rows
+// follow the T * kcap pair rows) where the pairs leave some of the experts empty, i.e. up to
+// five pairs per expert at capacity: its tiles then take the places of the absent ones, and
+// the fork, the join and two launches go (LLaDA2.0-mini shape, forward at T = 1 / 8 / 96: 68 /
+// 130 / 324 us forked, 42 / 118 / 306 us riding; host time of a forward 73 and 28 us).  With
+// every expert busy they would add a round to the grid (T = 200: 330 against 353 us).
+bool shared_joins(int T, int E, int f, int fs, int kcap) {
+  return fs == f && static_cast<long long>(T) * kcap <= 5LL * E;
+}
+
 bool make_layout(int T, int E, int d, int f, int fs, int kcap, Layout& L) {
   if (!valid_T(T) || !valid_E(E) || !valid_d(d) || !valid_f(f)) return false;
   if (fs != 0 && !valid_f(fs)) return false;
@@ -220,10 +230,13 @@ bool make_layout(int T, int E, int d, int f, int fs, int kcap, Layout& L) {
   L.pair_to_sorted = take(sizeof(int32_t) * cap);
   L.perm = take(permute_ws_bytes(static_cast<int>(cap), E));
   L.route_hist = take(route_fused_sorts(T, E) || route_block_sorts(T, E) ? route_hist_bytes(T, E) : 0);
-  L.swiglu = take(swiglu_ws_bytes(static_cast<int>(cap), E, f));
-  L.y = take(sizeof(uint16_t) * cap * d);
-  L.shared_act = fs ? take(swiglu_dense_ws_bytes(T, fs)) : o;
-  L.shared_y = fs ? take(sizeof(uint16_t) * static_cast<size_t>(T) * d) : o;
+  const bool joins = shared_joins(T, E, f, fs, kcap);
+  const size_t rows = cap + (joins ? T : 0);
+  L.swiglu = take(swiglu_ws_bytes(static_cast<int>(rows), f));
+  L.y = take(sizeof(uint16_t) * rows * d);
+  L.shared_act = fs && !joins ? take(swiglu_ws_bytes(T, fs)) : o;
+  L.shared_y = joins ? L.y + sizeof(uint16_t) * cap * d
+                     : (fs ? take(sizeof(uint16_t) * static_cast<size_t>(T) * d) : o);
   L.total = o;
   return true;
 }
@@ -305,7 +318,7 @@ size_t reflex_permute_workspace_size(int pair_capacity, int E) {
 
 size_t reflex_swiglu_workspace_size(int pair_capacity, int E, int f) {
   if (pair_capacity < 0 || !valid_E(E) || !valid_f(f)) return 0;
-  return swiglu_ws_bytes(pair_capacity, E, f);
+  return swiglu_ws_bytes(pair_capacity, f);
 }
 
 int reflex_router_logits(const uint16_t* h, const float* w_router, const float* bias,
@@ -387,7 +400,7 @@ int reflex_permute(const int32_t* pair_offsets, const int32_t* pair_expert, cons
   if (ws_bytes < permute_ws_bytes(pair_capacity, E)) return REFLEX_ERR_WORKSPACE;
   if (T == 0) return REFLEX_OK;
   return launch_permute(pair_offsets, pair_expert, pairs, T, E, pair_capacity, expert_offsets,
-                        sorted_token, pair_to_sorted, ws, nullptr, static_cast<hipStream_t>(stream));
+                        sorted_token, pair_to_sorted, ws, static_cast<hipStream_t>(stream));
 }
 
 int reflex_grouped_swiglu(const uint16_t* h, const int32_t* sorted_token,
@@ -399,10 +412,14 @@ int reflex_grouped_swiglu(const uint16_t* h, const int32_t* sorted_token,
   RFX_TRY(check_ptrs({sorted_token, expert_offsets}, 4));
   if (!valid_T(T) || !valid_E(E) || !valid_d(d) || !valid_f(f) || pair_capacity < 0)
     return REFLEX_ERR_SHAPE;
-  if (ws_bytes < swiglu_ws_bytes(pair_capacity, E, f)) return REFLEX_ERR_WORKSPACE;
+  if (ws_bytes < swiglu_ws_bytes(pair_capacity, f)) return REFLEX_ERR_WORKSPACE;
   if (T == 0 || pair_capacity == 0) return REFLEX_OK;
-  return launch_swiglu_routed(h, sorted_token, expert_offsets, w_gate, w_up, w_down, T, E, d, f,
-                              pair_capacity, y_sorted, ws, static_cast<hipStream_t>(stream));
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  uint16_t* act = static_cast<uint16_t*>(ws);
+  const AlwaysOn none{nullptr, nullptr, 0, 0};
+  RFX_TRY(launch_swiglu_up(h, sorted_token, expert_offsets, w_gate, w_up, T, E, d, f, pair_capacity,
+                           none, act, s));
+  return launch_swiglu_down(expert_offsets, w_down, T, E, d, f, pair_capacity, none, act, y_sorted, s);
 }
 
 int reflex_combine(const uint16_t* y_sorted, const int32_t* pair_offsets,
@@ -473,7 +490,7 @@ static int moe_forward_impl(const reflex_moe_args* a, void* ws, size_t ws_bytes,
   int32_t* sorted_token = static_cast<int32_t*>(at(L.sorted_token));
   int32_t* pair_to_sorted = static_cast<int32_t*>(at(L.pair_to_sorted));
   uint16_t* y = static_cast<uint16_t*>(at(L.y));
-  void* gws = at(L.swiglu);
+  uint16_t* act = static_cast<uint16_t*>(at(L.swiglu));
 
   // how the pairs get sorted: inside the route launch (its completion counter is zeroed
   // by the router launch), by the block-sort launches, or by the permutation launches
@@ -482,14 +499,17 @@ static int moe_forward_impl(const reflex_moe_args* a, void* ws, size_t ws_bytes,
   int32_t* route_hist =
       fused_sort || block_sort ? static_cast<int32_t*>(at(L.route_hist)) : nullptr;
   RFX_TRY(mark(0));
-  // The shared expert reads only h: on the side stream it runs beside the routing
-  // launches, which leave most CUs idle, and joins the caller's stream before the combine.
-  // The stage-timed variant keeps it in line, so that its stage time is its own.
+  // A shared expert that does not ride in the routed launches reads only h: on the side
+  // stream it runs beside the routing launches, which leave most CUs idle, and joins the
+  // caller's stream before the combine.  The stage-timed variant keeps it in line, so that
+  // its stage time is its own.
+  const bool joins = shared_joins(T, E, f, fs, kcap);
   uint16_t* shared_y_buf = fs ? static_cast<uint16_t*>(at(L.shared_y)) : nullptr;
+  uint16_t* shared_act = static_cast<uint16_t*>(at(L.shared_act));
   SideFork side(s);      // declared before any early return below: its exit joins
-  if (fs && ev == nullptr && may_fork && side.fork())
+  if (fs && !joins && ev == nullptr && may_fork && side.fork())
     RFX_TRY(launch_swiglu_dense(a->h, a->ws_gate, a->ws_up, a->ws_down, T, d, fs, shared_y_buf,
-                                at(L.shared_act), side.side()));
+                                shared_act, side.side()));
   const int32_t* k = a->k_in;
   // small layers: scores and counts in one launch (independent work side by side)
   const bool front = budget && front_fits(T, d);
@@ -541,34 +561,36 @@ static int moe_forward_impl(const reflex_moe_args* a, void* ws, size_t ws_bytes,
   RFX_TRY(mark(2));
   // pair offsets and TopK in one launch (P lives in pair_offsets[T]); for layers with
   // at most RF_HIST_MAX (token block, expert) counts the pairs are also sorted there,
-  // otherwise by the permutation launches.  Either way the sort writes the GEMM tile
-  // plan at the head of gws.
+  // otherwise by the permutation launches.
   RFX_TRY(launch_route_fused(scores, n_parts, static_cast<size_t>(T) * E, part_bias, scores_out, k,
                              T, E, kcap, a->norm_topk, pair_offsets, pair_expert,
                              pair_weight, a->pairs_out, done, route_hist,
-                             expert_offsets, sorted_token, pair_to_sorted,
-                             static_cast<int32_t*>(gws), s));
+                             expert_offsets, sorted_token, pair_to_sorted, s));
   RFX_TRY(mark(3));
   if (block_sort)
     RFX_TRY(launch_block_sort(pair_offsets, pair_expert, T, E, cap, route_hist, expert_offsets,
-                              sorted_token, pair_to_sorted, static_cast<int32_t*>(gws), s));
+                              sorted_token, pair_to_sorted, s));
   else if (!fused_sort)
     RFX_TRY(launch_permute(pair_offsets, pair_expert, pair_offsets + T, T, E, cap, expert_offsets,
-                           sorted_token, pair_to_sorted, at(L.perm), static_cast<int32_t*>(gws), s));
+                           sorted_token, pair_to_sorted, at(L.perm), s));
   RFX_TRY(mark(4));
+  const int sh_rows = joins ? T : 0;
   RFX_TRY(launch_swiglu_up(a->h, sorted_token, expert_offsets, a->w_gate, a->w_up, T, E, d, f,
-                           cap, gws, s));
+                           cap, AlwaysOn{a->ws_gate, a->ws_up, cap, sh_rows}, act, s));
   RFX_TRY(mark(5));
-  RFX_TRY(launch_swiglu_down(expert_offsets, a->w_down, E, d, f, cap, y, gws, s));
+  RFX_TRY(launch_swiglu_down(expert_offsets, a->w_down, T, E, d, f, cap,
+                             AlwaysOn{a->ws_down, nullptr, cap, sh_rows}, act, y, s));
   RFX_TRY(mark(6));
   const uint16_t* shared_y = nullptr;
-  if (fs && side.forked()) {
+  if (joins) {
+    shared_y = shared_y_buf;
+  } else if (fs && side.forked()) {
     RFX_TRY(side.join());
     shared_y = shared_y_buf;
   } else if (fs) {
     uint16_t* sy = shared_y_buf;
     RFX_TRY(launch_swiglu_dense(a->h, a->ws_gate, a->ws_up, a->ws_down, T, d, fs, sy,
-                                at(L.shared_act), s));
+                                shared_act, s));
     shared_y = sy;
   }
   RFX_TRY(mark(7));

@@ -12,7 +12,6 @@
 namespace rfx {
 
 constexpr int kWave = 64;
-constexpr int kGemmBM = 128;   // M tile (rows) of the grouped SwiGLU GEMM
 
 // ---- bf16 <-> fp32 ------------------------------------------------------------------
 RFX_DEVICE float bf16_to_f32(uint16_t b) { return __uint_as_float(static_cast<uint32_t>(b) << 16); }
@@ -213,38 +212,39 @@ bool route_block_sorts(int T, int E);
 size_t route_hist_bytes(int T, int E);
 int launch_block_sort(const int32_t* pair_offsets, const int32_t* pair_expert, int T, int E,
                       int cap, int32_t* hist, int32_t* expert_offsets, int32_t* sorted_token,
-                      int32_t* pair_to_sorted, int32_t* gemm_tile_off, hipStream_t s);
+                      int32_t* pair_to_sorted, hipStream_t s);
 int launch_route_fused(const float* logits, int n_parts, size_t part_stride, const float* bias,
                        float* logits_out, const int32_t* k, int T, int E, int k_max,
                        int norm_topk, int32_t* pair_offsets, int32_t* pair_expert,
                        float* pair_weight, int32_t* pairs_out, int32_t* done, int32_t* hist,
                        int32_t* expert_offsets, int32_t* sorted_token, int32_t* pair_to_sorted,
-                       int32_t* gemm_tile_off, hipStream_t s);
+                       hipStream_t s);
 
 size_t permute_ws_bytes(int pair_capacity, int E);
-// gemm_tile_off (nullable): also write the grouped GEMM's per-expert M-tile prefix.
 int launch_permute(const int32_t* pair_offsets, const int32_t* pair_expert, const int32_t* pairs,
                    int T, int E, int pair_capacity, int32_t* expert_offsets,
-                   int32_t* sorted_token, int32_t* pair_to_sorted, void* ws,
-                   int32_t* gemm_tile_off, hipStream_t s);
+                   int32_t* sorted_token, int32_t* pair_to_sorted, void* ws, hipStream_t s);
 
-size_t swiglu_ws_bytes(int pair_capacity, int E, int f);
-// Routed experts: rows grouped by expert_offsets, inputs gathered through sorted_token.
-int launch_swiglu_routed(const uint16_t* h, const int32_t* sorted_token,
-                         const int32_t* expert_offsets, const uint16_t* wg, const uint16_t* wu,
-                         const uint16_t* wd, int T, int E, int d, int f, int pair_capacity,
-                         uint16_t* y_sorted, void* ws, hipStream_t s);
-// The same in three steps: per-expert M-tile plan, gate/up GEMM, down GEMM.
-int launch_swiglu_plan(const int32_t* expert_offsets, int E, void* ws, hipStream_t s);
+// Bytes of the activation rows between the two GEMMs of M rows (or pairs).
+size_t swiglu_ws_bytes(int rows, int f);
+// Routed experts: rows grouped by expert_offsets, inputs gathered through sorted_token; act
+// and y_sorted hold cap rows.  An always-on expert of the same width may ride in the same
+// launches (rows == 0: none): every token is a row of it, in token order, at rows row0 ..
+// row0 + rows - 1 (row0 = cap) of act and y_sorted.  w0 / w1: its gate / up weights in the
+// up GEMM, its down weights / NULL in the down GEMM.
+struct AlwaysOn {
+  const uint16_t *w0, *w1;
+  int row0, rows;
+};
 int launch_swiglu_up(const uint16_t* h, const int32_t* sorted_token, const int32_t* expert_offsets,
                      const uint16_t* wg, const uint16_t* wu, int T, int E, int d, int f, int cap,
-                     void* ws, hipStream_t s);
-int launch_swiglu_down(const int32_t* expert_offsets, const uint16_t* wd, int E, int d, int f,
-                       int cap, uint16_t* y_sorted, void* ws, hipStream_t s);
+                     const AlwaysOn& sh, uint16_t* act, hipStream_t s);
+int launch_swiglu_down(const int32_t* expert_offsets, const uint16_t* wd, int T, int E, int d,
+                       int f, int cap, const AlwaysOn& sh, const uint16_t* act, uint16_t* y_sorted,
+                       hipStream_t s);
 // One dense expert over rows 0..M-1 of x (the always-on shared expert).
-size_t swiglu_dense_ws_bytes(int M, int f);
 int launch_swiglu_dense(const uint16_t* x, const uint16_t* wg, const uint16_t* wu,
-                        const uint16_t* wd, int M, int d, int f, uint16_t* y, void* ws,
+                        const uint16_t* wd, int M, int d, int f, uint16_t* y, uint16_t* act,
                         hipStream_t s);
 
 int launch_combine(const uint16_t* y_sorted, const int32_t* pair_offsets,

@@ -252,8 +252,7 @@ __global__ __launch_bounds__(TK_WAVES * kWave) void count_rule_kernel(
 // Permutation: stable counting sort of the token-major pair list by expert.
 //   1. per 1024-pair tile, an LDS histogram over experts
 //   2. one workgroup turns the [tile][expert] counts into start rows, expert-major
-//      then tile-minor, writes expert_offsets and (optionally) the grouped GEMM's
-//      per-expert M-tile prefix
+//      then tile-minor, and writes expert_offsets
 //   3. per tile: an LDS table of each pair's owning token, then 256-pair steps in
 //      which each wave finds the lanes holding the same expert with eight ballots
 //      (one per bit of the expert id) and ranks them by lane; the waves of a step
@@ -295,15 +294,13 @@ __global__ __launch_bounds__(PM_THREADS) void perm_hist_kernel(const int32_t* __
 
 // 1024 threads: group q = tid / 256 owns a contiguous quarter of the tiles, thread
 // e = tid % 256 one expert.  Group sums give expert totals; group 0 scans them into
-// expert_offsets (and the grouped GEMM's per-expert M-tile prefix); each group then
-// rewrites its tiles' counts as start rows (expert base + earlier groups + earlier
-// tiles of the group).
+// expert_offsets; each group then rewrites its tiles' counts as start rows (expert base +
+// earlier groups + earlier tiles of the group).
 __global__ __launch_bounds__(PM_SCAN_THREADS) void perm_scan_kernel(
-    int32_t* __restrict__ hist, int n_tiles, int E, int32_t* __restrict__ expert_offsets,
-    int32_t* __restrict__ gemm_tile_off) {
+    int32_t* __restrict__ hist, int n_tiles, int E, int32_t* __restrict__ expert_offsets) {
   __shared__ int s_part[4][REFLEX_MAX_EXPERTS];
   __shared__ int s_base[REFLEX_MAX_EXPERTS];
-  __shared__ int s_wave[8];
+  __shared__ int s_wave[4];
   const int tid = threadIdx.x, q = tid >> 8, e = tid & 255, lane = tid & 63, wv = tid >> 6;
   const int per = (n_tiles + 3) / 4;
   const int tb = q * per, te = min(n_tiles, tb + per);
@@ -314,33 +311,21 @@ __global__ __launch_bounds__(PM_SCAN_THREADS) void perm_scan_kernel(
   }
   s_part[q][e] = n;
   __syncthreads();
-  int tot = 0, incl = 0, tiles = 0, tincl = 0;
+  int tot = 0, incl = 0;
   if (q == 0) {            // waves 0..3
     tot = e < E ? s_part[0][e] + s_part[1][e] + s_part[2][e] + s_part[3][e] : 0;
-    tiles = (tot + kGemmBM - 1) / kGemmBM;
     incl = wave_inclusive_scan_i32(tot, lane);
-    tincl = wave_inclusive_scan_i32(tiles, lane);
-    if (lane == 63) {
-      s_wave[wv] = incl;
-      s_wave[4 + wv] = tincl;
-    }
+    if (lane == 63) s_wave[wv] = incl;
   }
   __syncthreads();
   if (q == 0) {
-    int off = 0, toff = 0;
-    for (int x = 0; x < wv; ++x) {
-      off += s_wave[x];
-      toff += s_wave[4 + x];
-    }
+    int off = 0;
+    for (int x = 0; x < wv; ++x) off += s_wave[x];
     const int base = off + incl - tot;
     s_base[e] = base;
     if (e < E) {
       expert_offsets[e] = base;
       if (e == E - 1) expert_offsets[E] = base + tot;
-      if (gemm_tile_off != nullptr) {
-        gemm_tile_off[e] = toff + tincl - tiles;
-        if (e == E - 1) gemm_tile_off[E] = toff + tincl;
-      }
     }
   }
   __syncthreads();
@@ -461,7 +446,7 @@ __global__ __launch_bounds__(PM_THREADS) void perm_scatter_kernel(
 
 // Small pair lists (capacity <= PS_MAX_CAP): the whole permutation in one
 // 1024-thread workgroup, with every pair's owning token in an LDS table: LDS
-// histogram, expert scan (+ GEMM tile plan), then 1024-pair steps ranked exactly as
+// histogram, expert scan, then 1024-pair steps ranked exactly as
 // in the per-tile scatter above, carrying each expert's running row across steps.
 // Saves two launches and their gaps where the list is short.
 constexpr int PS_THREADS = 1024;
@@ -471,13 +456,12 @@ constexpr int PS_MAX_CAP = 16384;
 __device__ __forceinline__ void perm_small_run(
     const int32_t* __restrict__ pair_offsets, const int32_t* __restrict__ pair_expert,
     const int32_t* __restrict__ pairs, int T, int cap, int E, int32_t* __restrict__ expert_offsets,
-    int32_t* __restrict__ sorted_token, int32_t* __restrict__ pair_to_sorted,
-    int32_t* __restrict__ gemm_tile_off) {
+    int32_t* __restrict__ sorted_token, int32_t* __restrict__ pair_to_sorted) {
   __shared__ int owner[PS_MAX_CAP];
   __shared__ uint8_t pexp[PS_MAX_CAP];           // each pair's expert (E <= 256)
   __shared__ int cnt[REFLEX_MAX_EXPERTS], run[REFLEX_MAX_EXPERTS];
   __shared__ int wcnt[PS_WAVES][REFLEX_MAX_EXPERTS];
-  __shared__ int s_wave[8];
+  __shared__ int s_wave[4];
   const int P = pair_count(pairs, cap);
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   for (int x = tid; x < PS_WAVES * REFLEX_MAX_EXPERTS; x += PS_THREADS) (&wcnt[0][0])[x] = 0;
@@ -494,33 +478,21 @@ __device__ __forceinline__ void perm_small_run(
     atomicAdd(&cnt[e], 1);
   }
   __syncthreads();
-  // expert scan (waves 0..3, one expert per thread) and the GEMM's M-tile prefix
-  int n = 0, incl = 0, tiles = 0, tincl = 0;
+  // expert scan (waves 0..3, one expert per thread)
+  int n = 0, incl = 0;
   if (tid < REFLEX_MAX_EXPERTS) {
     n = tid < E ? cnt[tid] : 0;
-    tiles = (n + kGemmBM - 1) / kGemmBM;
     incl = wave_inclusive_scan_i32(n, lane);
-    tincl = wave_inclusive_scan_i32(tiles, lane);
-    if (lane == 63) {
-      s_wave[wv] = incl;
-      s_wave[4 + wv] = tincl;
-    }
+    if (lane == 63) s_wave[wv] = incl;
   }
   __syncthreads();
   if (tid < E) {
-    int off = 0, toff = 0;
-    for (int x = 0; x < wv; ++x) {
-      off += s_wave[x];
-      toff += s_wave[4 + x];
-    }
+    int off = 0;
+    for (int x = 0; x < wv; ++x) off += s_wave[x];
     const int base = off + incl - n;
     run[tid] = base;
     expert_offsets[tid] = base;
     if (tid == E - 1) expert_offsets[E] = base + n;
-    if (gemm_tile_off != nullptr) {
-      gemm_tile_off[tid] = toff + tincl - tiles;
-      if (tid == E - 1) gemm_tile_off[E] = toff + tincl;
-    }
   }
   __syncthreads();
   const uint64_t lt_mask = (1ull << lane) - 1ull;
@@ -566,10 +538,9 @@ __device__ __forceinline__ void perm_small_run(
 __global__ __launch_bounds__(PS_THREADS) void perm_small_kernel(
     const int32_t* __restrict__ pair_offsets, const int32_t* __restrict__ pair_expert,
     const int32_t* __restrict__ pairs, int T, int cap, int E, int32_t* __restrict__ expert_offsets,
-    int32_t* __restrict__ sorted_token, int32_t* __restrict__ pair_to_sorted,
-    int32_t* __restrict__ gemm_tile_off) {
+    int32_t* __restrict__ sorted_token, int32_t* __restrict__ pair_to_sorted) {
   perm_small_run(pair_offsets, pair_expert, pairs, T, cap, E, expert_offsets, sorted_token,
-                 pair_to_sorted, gemm_tile_off);
+                 pair_to_sorted);
 }
 
 // ------------------------------------------------------------------------------------
@@ -581,7 +552,7 @@ __global__ __launch_bounds__(PS_THREADS) void perm_small_kernel(
 // keeps (token, rank) in pair_to_sorted and its per-expert counts in hist[b][.]; the
 // workgroup that finishes last (agent-scope acquire-release counter, so every other
 // workgroup's pairs are visible to it) turns hist into per-(workgroup, expert) start
-// rows, writes expert_offsets and the GEMM tile plan, and scatters every pair to
+// rows, writes expert_offsets, and scatters every pair to
 //   expert_offsets[e] + start[b][e] + rank,
 // the same stable (expert, token) order as the permutation kernels.  It then resets the
 // counter to zero, which is where the launch before this one left it.
@@ -599,8 +570,7 @@ __global__ __launch_bounds__(RF_WAVES * kWave) void route_fused_kernel(
     int norm_topk, int32_t* __restrict__ pair_offsets, int32_t* __restrict__ pair_expert,
     float* __restrict__ pair_weight, int32_t* __restrict__ pairs_out, int32_t* __restrict__ done,
     int32_t* __restrict__ hist, int32_t* __restrict__ expert_offsets,
-    int32_t* __restrict__ sorted_token, int32_t* __restrict__ pair_to_sorted,
-    int32_t* __restrict__ gemm_tile_off) {
+    int32_t* __restrict__ sorted_token, int32_t* __restrict__ pair_to_sorted) {
   __shared__ int s_before[RF_WAVES], s_cnt[RF_WAVES];
   __shared__ uint32_t s_mask[REFLEX_MAX_EXPERTS];
   __shared__ int s_last;
@@ -670,7 +640,7 @@ __global__ __launch_bounds__(RF_WAVES * kWave) void route_fused_kernel(
   __shared__ int s_tab[RF_HIST_MAX];
   __shared__ int s_part[RF_WAVES][REFLEX_MAX_EXPERTS];
   __shared__ int s_eo[REFLEX_MAX_EXPERTS];
-  __shared__ int s_wave[8];
+  __shared__ int s_wave[4];
   constexpr int RF_THREADS = RF_WAVES * kWave;
   constexpr int RF_TAB_PT = RF_HIST_MAX / RF_THREADS;     // table words per thread, at most
   const int G = gridDim.x, n_tab = G * E;
@@ -722,29 +692,19 @@ __global__ __launch_bounds__(RF_WAVES * kWave) void route_fused_kernel(
   }
   __syncthreads();
   const int tot = tid < E ? s_eo[tid] : 0;
-  int incl = 0, tiles = 0, tincl = 0;
+  int incl = 0;
   if (tid < REFLEX_MAX_EXPERTS) {
-    tiles = (tot + kGemmBM - 1) / kGemmBM;
     incl = wave_inclusive_scan_i32(tot, lane);
-    tincl = wave_inclusive_scan_i32(tiles, lane);
-    if (lane == 63) {
-      s_wave[wv] = incl;
-      s_wave[4 + wv] = tincl;
-    }
+    if (lane == 63) s_wave[wv] = incl;
   }
   __syncthreads();
   if (tid < E) {
-    int eoff = 0, toff = 0;
-    for (int x = 0; x < wv; ++x) {
-      eoff += s_wave[x];
-      toff += s_wave[4 + x];
-    }
+    int eoff = 0;
+    for (int x = 0; x < wv; ++x) eoff += s_wave[x];
     const int ebase = eoff + incl - tot;
     s_eo[tid] = ebase;
     expert_offsets[tid] = ebase;
     if (tid == E - 1) expert_offsets[E] = ebase + tot;
-    gemm_tile_off[tid] = toff + tincl - tiles;
-    if (tid == E - 1) gemm_tile_off[E] = toff + tincl;
   }
   __syncthreads();
   // the scatter: pair p of workgroup w's token t with rank r in its expert e goes to
@@ -775,8 +735,7 @@ __global__ __launch_bounds__(RF_WAVES * kWave) void route_fused_kernel(
 //   column scan: workgroup e turns row e of cnt into start rows (the pairs of expert e
 //   in earlier blocks), in place, and writes the expert's total to tot[e];
 //   scatter: every workgroup scans the E totals into expert bases (workgroup 0 also
-//   writes them as expert_offsets, with the GEMM tile plan) and sends each pair of its
-//   block b to base[e] + start[e][b] + rank.
+//   writes them as expert_offsets) and sends each pair of its block b to base[e] + start[e][b] + rank.
 // ------------------------------------------------------------------------------------
 constexpr int BS_THREADS = 1024;
 constexpr long BS_MAX_COUNTS = 1L << 20;   // (block, expert) counts the block sort takes
@@ -810,10 +769,10 @@ __global__ __launch_bounds__(BS_THREADS) void block_colscan_kernel(int32_t* __re
 __global__ __launch_bounds__(256) void block_scatter_kernel(
     const int32_t* __restrict__ pair_offsets, const int32_t* __restrict__ pair_expert, int T,
     int cap, int E, int G, const int32_t* __restrict__ start, const int32_t* __restrict__ tot,
-    int32_t* __restrict__ expert_offsets, int32_t* __restrict__ gemm_tile_off,
-    int32_t* __restrict__ sorted_token, int32_t* __restrict__ pair_to_sorted) {
+    int32_t* __restrict__ expert_offsets, int32_t* __restrict__ sorted_token,
+    int32_t* __restrict__ pair_to_sorted) {
   __shared__ int s_base[REFLEX_MAX_EXPERTS];
-  __shared__ int s_wave[8];
+  __shared__ int s_wave[4];
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int t0 = b * RF_WAVES, t1 = min(T, t0 + RF_WAVES);
   int p0 = pair_offsets[t0], p1 = pair_offsets[t1];
@@ -822,26 +781,16 @@ __global__ __launch_bounds__(256) void block_scatter_kernel(
   const int n = tid < E ? tot[tid] : 0;
   const int st = tid < E ? start[static_cast<size_t>(tid) * G + b] : 0;
   const int incl = wave_inclusive_scan_i32(n, lane);
-  const int tiles = (n + kGemmBM - 1) / kGemmBM;
-  const int tincl = b == 0 ? wave_inclusive_scan_i32(tiles, lane) : 0;
-  if (lane == 63) {
-    s_wave[wv] = incl;
-    s_wave[4 + wv] = tincl;
-  }
+  if (lane == 63) s_wave[wv] = incl;
   __syncthreads();
   if (tid < E) {
-    int eoff = 0, toff = 0;
-    for (int x = 0; x < wv; ++x) {
-      eoff += s_wave[x];
-      toff += s_wave[4 + x];
-    }
+    int eoff = 0;
+    for (int x = 0; x < wv; ++x) eoff += s_wave[x];
     const int base = eoff + incl - n;
     s_base[tid] = base + st;
     if (b == 0) {
       expert_offsets[tid] = base;
       if (tid == E - 1) expert_offsets[E] = base + n;
-      gemm_tile_off[tid] = toff + tincl - tiles;
-      if (tid == E - 1) gemm_tile_off[E] = toff + tincl;
     }
   }
   p0 = p0 < 0 ? 0 : (p0 > cap ? cap : p0);
@@ -904,13 +853,13 @@ size_t route_hist_bytes(int T, int E) {     // the counts, and the block sort's 
 
 int launch_block_sort(const int32_t* pair_offsets, const int32_t* pair_expert, int T, int E,
                       int cap, int32_t* hist, int32_t* expert_offsets, int32_t* sorted_token,
-                      int32_t* pair_to_sorted, int32_t* gemm_tile_off, hipStream_t s) {
+                      int32_t* pair_to_sorted, hipStream_t s) {
   if (T <= 0) return REFLEX_OK;
   const int G = (T + RF_WAVES - 1) / RF_WAVES;
   int32_t* tot = hist + static_cast<size_t>(G) * E;
   hipLaunchKernelGGL(block_colscan_kernel, dim3(E), dim3(BS_THREADS), 0, s, hist, G, tot);
   hipLaunchKernelGGL(block_scatter_kernel, dim3(G), dim3(256), 0, s, pair_offsets, pair_expert, T,
-                     cap, E, G, hist, tot, expert_offsets, gemm_tile_off, sorted_token,
+                     cap, E, G, hist, tot, expert_offsets, sorted_token,
                      pair_to_sorted);
   return launch_status();
 }
@@ -920,7 +869,7 @@ int launch_route_fused(const float* logits, int n_parts, size_t part_stride, con
                        int norm_topk, int32_t* pair_offsets, int32_t* pair_expert,
                        float* pair_weight, int32_t* pairs_out, int32_t* done, int32_t* hist,
                        int32_t* expert_offsets, int32_t* sorted_token, int32_t* pair_to_sorted,
-                       int32_t* gemm_tile_off, hipStream_t s) {
+                       hipStream_t s) {
   const bool sort = done != nullptr;
   auto kernel = sort ? route_fused_kernel<4, true> : route_fused_kernel<4, false>;
   switch (topk_slots(E)) {
@@ -931,7 +880,7 @@ int launch_route_fused(const float* logits, int n_parts, size_t part_stride, con
   }
   hipLaunchKernelGGL(kernel, dim3((T + RF_WAVES - 1) / RF_WAVES), dim3(RF_WAVES * kWave), 0, s, logits,
                      n_parts, part_stride, bias, logits_out, k, T, E, k_max, norm_topk, pair_offsets, pair_expert, pair_weight, pairs_out, done,
-                     hist, expert_offsets, sorted_token, pair_to_sorted, gemm_tile_off);
+                     hist, expert_offsets, sorted_token, pair_to_sorted);
   return launch_status();
 }
 
@@ -943,10 +892,10 @@ size_t permute_ws_bytes(int pair_capacity, int E) {
 
 int launch_permute(const int32_t* pair_offsets, const int32_t* pair_expert, const int32_t* pairs,
                    int T, int E, int cap, int32_t* expert_offsets, int32_t* sorted_token,
-                   int32_t* pair_to_sorted, void* ws, int32_t* gemm_tile_off, hipStream_t s) {
+                   int32_t* pair_to_sorted, void* ws, hipStream_t s) {
   if (cap <= PS_MAX_CAP) {
     hipLaunchKernelGGL(perm_small_kernel, dim3(1), dim3(PS_THREADS), 0, s, pair_offsets, pair_expert,
-                       pairs, T, cap, E, expert_offsets, sorted_token, pair_to_sorted, gemm_tile_off);
+                       pairs, T, cap, E, expert_offsets, sorted_token, pair_to_sorted);
     return launch_status();
   }
   const int n_tiles = perm_tiles(cap);
@@ -954,7 +903,7 @@ int launch_permute(const int32_t* pair_offsets, const int32_t* pair_expert, cons
   hipLaunchKernelGGL(perm_hist_kernel, dim3(n_tiles), dim3(PM_THREADS), 0, s, pair_expert, pairs,
                      cap, E, hist);
   hipLaunchKernelGGL(perm_scan_kernel, dim3(1), dim3(PM_SCAN_THREADS), 0, s, hist, n_tiles, E,
-                     expert_offsets, gemm_tile_off);
+                     expert_offsets);
   hipLaunchKernelGGL(perm_scatter_kernel, dim3(n_tiles), dim3(PM_THREADS), 0, s, pair_offsets,
                      pair_expert, pairs, T, cap, E, hist, sorted_token, pair_to_sorted);
   return launch_status();

@@ -1,0 +1,139 @@
+"""The tile shapes of the grouped SwiGLU GEMM and the always-on expert's place in its
+launches, at the sizes where they can go wrong: tile edges, remainders, K loops shorter than
+the copy lookahead, operands beyond 32-bit byte offsets.  Every row against the fp64
+definition, with the layer's bar (bf16 rounding of activation and output)."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+from gpu_common import layer_tolerance_check, note, require_gpu
+from synth.device import bf16_bits, state_tensors, to_device
+from synth.workloads import bf16_bits_from_f32, make_fuzz_workload
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    return require_gpu()
+
+
+# T (rows of h), experts, d, f, the rows of the first experts (the rest: random below `most`)
+SHAPES = [
+    # up to 32 tokens, 32 x 64 tiles: edges of 32 rows, partial N tiles, more rows than tokens
+    (32, 40, 384, 192, [0, 1, 31, 32, 33, 65, 100], 20),
+    (1, 7, 128, 64, [0, 1, 0, 1], 2),             # one token, K loops of 2 and 1 steps
+    (20, 12, 256, 128, [33, 0, 32], 40),          # K loops of 4 and 2 steps
+    # up to 64 tokens, 64 x 128 tiles
+    (64, 24, 384, 320, [0, 1, 63, 64, 65, 129, 200], 70),
+    (50, 256, 128, 64, [64, 0, 65], 10),          # 256 experts, K loops of 2 and 1 steps
+    # few 256-row tiles: 32-row and 64-row tiles with many rows an expert
+    (300, 3, 256, 64, [500, 0, 33], 10),
+    (1200, 5, 640, 320, [512, 511, 1, 0, 257], 10),
+    # 256 x 256 tiles
+    (900, 100, 640, 320, [0, 1, 31, 33, 255, 256, 257, 511, 512, 513, 700], 120),
+    (200, 160, 128, 64, [256, 257, 0, 1], 40),    # K loops of 2 and 1 steps
+    (200, 256, 256, 128, [300, 0, 255], 30),      # K loops of 4 and 2 steps
+]
+
+
+@pytest.mark.parametrize("case", range(len(SHAPES)))
+def test_tile_shapes(torch, case):
+    from paper_2608_01784_amd import _lib as L
+    T, E, d, f, first, most = SHAPES[case]
+    rng = np.random.default_rng([case, 41])
+    counts = rng.integers(0, most, E)
+    counts[:len(first)] = first
+    P = int(counts.sum())
+    eo = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    st = rng.integers(0, T, P).astype(np.int32)
+
+    def bf16(shape, scale):
+        return bf16_bits_from_f32((rng.standard_normal(shape) * scale).astype(np.float32))
+
+    h, wg, wu = bf16((T, d), 1.0), bf16((E, f, d), d ** -0.5), bf16((E, f, d), d ** -0.5)
+    wd = bf16((E, d, f), 0.3 * f ** -0.5)
+    cap = P + 5
+    y = torch.full((cap, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    ws = torch.empty(L.reflex_swiglu_workspace_size(cap, E, f), dtype=torch.uint8, device="cuda")
+    L.reflex_grouped_swiglu(to_device(h), to_device(np.concatenate([st, np.zeros(5, np.int32)])),
+                            to_device(eo), to_device(wg), to_device(wu), to_device(wd), y, ws)
+    torch.cuda.synchronize()
+    yb = bf16_bits(y)
+    got, ref = [], []
+    for e in np.flatnonzero(counts):
+        rows = np.arange(eo[e], eo[e + 1])
+        ref.append(oracle.swiglu_expert(oracle.bf16_to_f64(h[st[rows]]), oracle.bf16_to_f64(wg[e]),
+                                        oracle.bf16_to_f64(wu[e]), oracle.bf16_to_f64(wd[e])))
+        got.append(oracle.bf16_to_f64(yb[rows]))
+    layer_tolerance_check(np.concatenate(got), np.concatenate(ref), f"T={T} E={E} d={d} f={f} P={P}")
+    assert np.isnan(oracle.bf16_to_f64(yb[P:])).all()      # rows past P untouched
+
+
+@pytest.mark.parametrize("which", ["up", "down"])
+def test_operands_past_32_bit_offsets(torch, which):
+    # 2^30 elements or more: the input rows go through 64-bit addresses.  up: tokens at the
+    # far end of a 2^20 x 1024 h; down: 2^20 activation rows of width 1024.
+    from paper_2608_01784_amd import _lib as L
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    T, d, f, E = (1 << 20, 1024, 64, 2) if which == "up" else (500, 128, 1024, 2)
+    P = 700 if which == "up" else (1 << 20) + 300
+
+    def normal(shape, scale):
+        return (torch.randn(shape, generator=g, device="cuda") * scale).to(torch.bfloat16)
+
+    h = torch.empty((T, d), dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    wg, wu = normal((E, f, d), d ** -0.5), normal((E, f, d), d ** -0.5)
+    wd = normal((E, d, f), 0.3 * f ** -0.5)
+    st = torch.randint(max(0, T - 1000), T, (P,), generator=g, device="cuda", dtype=torch.int32)
+    cut = P // 2 + 17
+    eo = torch.tensor([0, cut, P], dtype=torch.int32, device="cuda")
+    y = torch.empty((P, d), dtype=torch.bfloat16, device="cuda")
+    ws = torch.empty(L.reflex_swiglu_workspace_size(P, E, f), dtype=torch.uint8, device="cuda")
+    print(f"operands past 32-bit offsets: {which}", flush=True)
+    L.reflex_grouped_swiglu(h, st, eo, wg, wu, wd, y, ws)
+    torch.cuda.synchronize()
+    rows = np.unique(np.concatenate([np.linspace(0, P - 1, 400).astype(np.int64),
+                                     np.arange(cut - 3, cut + 3), np.arange(P - 40, P)]))
+    pick = torch.from_numpy(rows).cuda()
+    x = h[st[pick].long()].double().cpu().numpy()
+    ref = np.empty((len(rows), d))
+    for e, m in ((0, rows < cut), (1, rows >= cut)):
+        ref[m] = oracle.swiglu_expert(x[m], *(w[e].double().cpu().numpy() for w in (wg, wu, wd)))
+    layer_tolerance_check(y[pick].double().cpu().numpy(), ref, f"{which} past 32-bit offsets")
+
+
+@pytest.mark.parametrize("T,E,kmax,fs", [
+    (24, 64, 12, 128),      # rides, 32-row tiles
+    (60, 256, 12, 128),     # rides, 64-row tiles
+    (105, 256, 12, 128),    # rides, 256-row tiles
+    (107, 256, 12, 128),    # just past the rule: launches of its own, 128-row tiles
+    (40, 16, 4, 192),       # another width: launches of its own, 64-row tiles
+    (2100, 16, 4, 128),     # launches of its own, 256-row tiles
+])
+@pytest.mark.parametrize("no_pairs", [False, True])
+def test_always_on_expert(torch, T, E, kmax, fs, no_pairs):
+    from paper_2608_01784_amd.layer import ExpertWeights, MoELayer, TokenState
+    w = make_fuzz_workload(300 + T, T=T, d=256, E=E, f=128, f_shared=fs, k_max=kmax)
+    dw = {"w_gate": to_device(w.w_gate()), "w_up": to_device(w.w_up()), "w_down": to_device(w.w_down()),
+          "w_router": to_device(w.w_router()),
+          "router_bias": None if w.router_bias is None else to_device(w.router_bias)}
+    shared = w.shared_weights()
+    dw["ws_gate"], dw["ws_up"], dw["ws_down"] = (to_device(x) for x in shared)
+    lay = MoELayer(w.T, w.d, ExpertWeights(**dw), w.params)
+    st = TokenState(**state_tensors(w))
+    k_in = np.zeros(w.T, np.int32) if no_pairs else None
+    out = lay.forward(to_device(w.h), st, k_in=None if k_in is None else to_device(k_in))
+    torch.cuda.synchronize()
+    assert int(lay.pairs.item()) == (0 if no_pairs else int(lay.k.sum().item()))
+    k = np.zeros(w.T, np.int64) if no_pairs else lay.k.cpu().numpy()
+    route = oracle.topk_route(lay.logits.cpu().numpy().astype(np.float64), k)
+    wg, wu, wd = w.w_gate(), w.w_up(), w.w_down()
+    toks = np.arange(w.T) if T < 1000 else np.unique(np.linspace(0, w.T - 1, 600).astype(int))
+    ref = oracle.moe_layer(w.h, route, lambda e: (wg[e], wu[e], wd[e]), w.E, shared=shared, tokens=toks)
+    layer_tolerance_check(oracle.bf16_to_f64(bf16_bits(out))[toks], ref,
+                          f"always-on expert T={T} E={E} fs={fs} no_pairs={no_pairs}")
+    note("ok")
