@@ -373,7 +373,8 @@ int reflex_count_rule(const float* logits, int T, int E, int rule, float thresho
     return REFLEX_ERR_SHAPE;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (T == 0) return pairs_out ? launch_fill_i32(pairs_out, 0, 1, s) : REFLEX_OK;
-  return launch_count_rule(logits, T, E, rule, threshold, k_min, k_max, k_out, pairs_out, s);
+  return launch_count_rule(logits, 1, 0, nullptr, nullptr, T, E, rule, threshold, k_min, k_max,
+                           k_out, pairs_out, s);
 }
 
 int reflex_topk_variable(const float* logits, const int32_t* k, int T, int E, int k_max,
@@ -511,61 +512,53 @@ static int moe_forward_impl(const reflex_moe_args* a, void* ws, size_t ws_bytes,
     RFX_TRY(launch_swiglu_dense(a->h, a->ws_gate, a->ws_up, a->ws_down, T, d, fs, shared_y_buf,
                                 shared_act, side.side()));
   const int32_t* k = a->k_in;
-  // small layers: scores and counts in one launch (independent work side by side)
-  const bool front = budget && front_fits(T, d);
-  // score source of the route kernel: finished scores, or the front launch's partials
-  const float* scores = logits;
+  int32_t* kb = a->k_out ? a->k_out : static_cast<int32_t*>(at(L.k));
+  // score source of the route kernel: finished scores, or the K slices' partials
+  const size_t te = static_cast<size_t>(T) * E;
+  float* parts = static_cast<float*>(at(L.logits));
+  const float* scores = parts;
   int n_parts = 1;
-  const float* part_bias = nullptr;
-  float* scores_out = nullptr;
-  if (front) {
-    int32_t* kb = a->k_out ? a->k_out : static_cast<int32_t*>(at(L.k));
-    float* parts = static_cast<float*>(at(L.logits));
-    RFX_TRY(launch_front(a->h, a->w_router, parts, T, d, E, a->block_idx, a->masked, a->hist_len,
-                         a->conf_prev1, a->conf_prev2, a->seq_offsets, a->active_block, a->B,
-                         a->params, kb, s, done));
-    k = kb;
-    scores = parts;
+  bool partial = true;      // the partials are to be added yet, and the bias
+  if (front_fits(T, d)) {
+    // small layers: score tiles over K slices, and the REFLEX counts beside them
     n_parts = front_slices(d);
-    part_bias = a->router_bias;
-    scores_out = a->logits_out;
+    RFX_TRY(launch_front(a->h, a->w_router, parts, T, d, E, a->block_idx, a->masked, a->hist_len,
+                         a->conf_prev1, a->conf_prev2, a->seq_offsets, a->active_block,
+                         budget ? a->B : 0, a->params, kb, s, done));
+    if (budget) k = kb;
+  } else if ((n_parts = router_slices(T, d, E)) > 1) {
+    RFX_TRY(launch_router(a->h, a->w_router, a->router_bias, parts, T, d, E, s, done, n_parts));
   } else {
-    // partial scores for the route kernel to add, unless a count rule reads the scores
-    const int ns = by_rule ? 1 : router_slices(T, d, E);
-    if (ns > 1) {
-      float* parts = static_cast<float*>(at(L.logits));
-      RFX_TRY(launch_router(a->h, a->w_router, a->router_bias, parts, T, d, E, s, done, ns));
-      scores = parts;
-      n_parts = ns;
-      part_bias = a->router_bias;
-      scores_out = a->logits_out;
-    } else {
-      RFX_TRY(launch_router(a->h, a->w_router, a->router_bias, logits, T, d, E, s, done));
-    }
+    scores = logits;
+    partial = false;
+    RFX_TRY(launch_router(a->h, a->w_router, a->router_bias, logits, T, d, E, s, done));
   }
+  const float* part_bias = partial ? a->router_bias : nullptr;
+  float* scores_out = partial ? a->logits_out : nullptr;
   RFX_TRY(mark(1));
-  if (k == nullptr) {
-    int32_t* kb = a->k_out ? a->k_out : static_cast<int32_t*>(at(L.k));
-    if (a->uniform_k > 0) {
-      RFX_TRY(launch_fill_i32(kb, a->uniform_k, T, s));
-    } else if (by_rule) {
-      RFX_TRY(launch_count_rule(logits, T, E, a->k_rule, a->k_threshold, a->params.k_min,
-                                a->params.k_max, kb, nullptr, s));
-    } else {
-      RFX_TRY(launch_budget(a->block_idx, a->masked, a->hist_len, a->conf_prev1, a->conf_prev2,
-                            a->seq_offsets, a->active_block, a->B, T, a->params, kb, nullptr,
-                            nullptr, s));
-    }
+  if (k == nullptr && by_rule) {
+    // the rule needs whole rows of scores: it adds the partials and leaves finished scores
+    RFX_TRY(launch_count_rule(scores, n_parts, te, part_bias, partial ? logits : nullptr, T, E,
+                              a->k_rule, a->k_threshold, a->params.k_min, a->params.k_max, kb,
+                              nullptr, s));
+    scores = logits;
+    n_parts = 1;
+    part_bias = nullptr;
+    scores_out = nullptr;
     k = kb;
-  }
+  } else if (k == nullptr && budget) {
+    RFX_TRY(launch_budget(a->block_idx, a->masked, a->hist_len, a->conf_prev1, a->conf_prev2,
+                          a->seq_offsets, a->active_block, a->B, T, a->params, kb, nullptr,
+                          nullptr, s));
+    k = kb;
+  }     // (uniform counts: the route kernel fills them in)
   RFX_TRY(mark(2));
   // pair offsets and TopK in one launch (P lives in pair_offsets[T]); for layers with
   // at most RF_HIST_MAX (token block, expert) counts the pairs are also sorted there,
   // otherwise by the permutation launches.
-  RFX_TRY(launch_route_fused(scores, n_parts, static_cast<size_t>(T) * E, part_bias, scores_out, k,
-                             T, E, kcap, a->norm_topk, pair_offsets, pair_expert,
-                             pair_weight, a->pairs_out, done, route_hist,
-                             expert_offsets, sorted_token, pair_to_sorted, s));
+  RFX_TRY(launch_route_fused(scores, n_parts, te, part_bias, scores_out, k, a->k_out, T, E, kcap,
+                             a->norm_topk, pair_offsets, pair_expert, pair_weight, a->pairs_out,
+                             done, route_hist, expert_offsets, sorted_token, pair_to_sorted, s));
   RFX_TRY(mark(3));
   if (block_sort)
     RFX_TRY(launch_block_sort(pair_offsets, pair_expert, T, E, cap, route_hist, expert_offsets,

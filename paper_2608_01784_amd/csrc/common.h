@@ -169,7 +169,8 @@ int launch_budget(const int32_t* block_idx, const uint8_t* masked, const int8_t*
 
 int launch_fill_i32(int32_t* dst, int32_t value, int n, hipStream_t s);
 
-// Router scores and REFLEX counts in one launch; only for shapes where front_fits().
+// Router scores and REFLEX counts (B = 0: the scores alone) in one launch; only for shapes
+// where front_fits().
 // The scores come out as front_slices(d) fp32 partials without the bias, parts[s][T][E]
 // (slice s covers d columns [256 s, 256 s + 256)); a score is the partials added in
 // slice order, plus the bias.
@@ -191,7 +192,10 @@ int launch_count_scan(const int32_t* k, int T, int k_max, int32_t* pair_offsets,
                       int32_t* pairs_out, hipStream_t s);
 
 // Score-derived counts (REFLEX_RULE_TOP_P / REFLEX_RULE_THRESHOLD); pairs_out nullable.
-int launch_count_rule(const float* logits, int T, int E, int rule, float threshold, int k_min,
+// The scores as in launch_route_fused; `finished` (nullable, and may be `logits`) receives the
+// added scores.
+int launch_count_rule(const float* logits, int n_parts, size_t part_stride, const float* bias,
+                      float* finished, int T, int E, int rule, float threshold, int k_min,
                       int k_max, int32_t* k_out, int32_t* pairs_out, hipStream_t s);
 
 int launch_topk(const float* logits, const int32_t* k, int T, int E, int k_max, int norm_topk,
@@ -206,7 +210,8 @@ int launch_topk(const float* logits, const int32_t* k, int T, int E, int k_max, 
 //  - otherwise hist and done NULL, and launch_permute follows.
 // pairs_out nullable.  The scores are n_parts partials part_stride floats apart, added
 // in order, plus bias (nullable); n_parts = 1 with bias NULL reads finished scores.
-// logits_out (nullable) receives the finished scores.
+// logits_out (nullable) receives the finished scores.  k NULL: every count is k_max, written
+// to k_out (nullable).
 bool route_fused_sorts(int T, int E);
 bool route_block_sorts(int T, int E);
 size_t route_hist_bytes(int T, int E);
@@ -214,8 +219,8 @@ int launch_block_sort(const int32_t* pair_offsets, const int32_t* pair_expert, i
                       int cap, int32_t* hist, int32_t* expert_offsets, int32_t* sorted_token,
                       int32_t* pair_to_sorted, hipStream_t s);
 int launch_route_fused(const float* logits, int n_parts, size_t part_stride, const float* bias,
-                       float* logits_out, const int32_t* k, int T, int E, int k_max,
-                       int norm_topk, int32_t* pair_offsets, int32_t* pair_expert,
+                       float* logits_out, const int32_t* k, int32_t* k_out, int T, int E,
+                       int k_max, int norm_topk, int32_t* pair_offsets, int32_t* pair_expert,
                        float* pair_weight, int32_t* pairs_out, int32_t* done, int32_t* hist,
                        int32_t* expert_offsets, int32_t* sorted_token, int32_t* pair_to_sorted,
                        hipStream_t s);

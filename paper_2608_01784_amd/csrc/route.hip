@@ -30,7 +30,7 @@ struct TopkRow {
 // tiles of the fused router + budget launch): they are added in order, then the bias
 // (nullable).  n_parts = 1 with no bias reads finished scores.
 template <int NX>
-__device__ __forceinline__ TopkRow<NX> topk_load(const float* __restrict__ row, int E,
+__device__ __forceinline__ TopkRow<NX> topk_load(const float* row, int E,
                                                  int n_parts = 1, size_t part_stride = 0,
                                                  const float* __restrict__ bias = nullptr) {
   const int lane = threadIdx.x & 63;
@@ -178,36 +178,37 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
   return v;
 }
 
+// The scores may arrive as partials (topk_load); `finished` (nullable) then receives the
+// added scores, and may be the first partial: a wave has read all of its row by then.
+template <int NX>
 __global__ __launch_bounds__(TK_WAVES * kWave) void count_rule_kernel(
-    const float* __restrict__ logits, int T, int E, int rule, double thr, int k_min, int k_max,
+    const float* logits, int n_parts, size_t part_stride, const float* __restrict__ bias,
+    float* finished, int T, int E, int rule, double thr, int k_min, int k_max,
     int32_t* __restrict__ k_out, int32_t* __restrict__ pairs_out) {
   const int lane = threadIdx.x & 63;
   const int i = blockIdx.x * TK_WAVES + (threadIdx.x >> 6);
   if (i >= T) return;
-  const float* row = logits + static_cast<size_t>(i) * E;
-  uint64_t key[4];
-  float val[4];
-  uint64_t best = 0;
-  float v[4];
+  const TopkRow<NX> row = topk_load<NX>(logits + static_cast<size_t>(i) * E, E, n_parts, part_stride, bias);
+  if (finished != nullptr) {
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {     // unconditional loads, all in flight together
-    const int e = lane + kWave * j;
-    v[j] = row[e < E ? e : E - 1];
+    for (int j = 0; j < NX; ++j)
+      if (lane + kWave * j < E) finished[static_cast<size_t>(i) * E + lane + kWave * j] = row.val[j];
   }
+  uint64_t key[NX];
+  uint64_t best = 0;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
+  for (int j = 0; j < NX; ++j) {
     const int e = lane + kWave * j;
-    val[j] = e < E ? v[j] : 0.0f;
-    key[j] = e < E ? (static_cast<uint64_t>(f32_order_key(val[j])) << 32) | (0xffffu - e) : 0;
+    key[j] = e < E ? (static_cast<uint64_t>(row.key[j]) << 32) | (0xffffu - e) : 0;
     best = key[j] > best ? key[j] : best;
   }
   best = wave_max_u64(best);
   const double rmax = static_cast<double>(f32_from_order_key(static_cast<uint32_t>(best >> 32)));
-  double ex[4];
+  double ex[NX];
   double part = 0.0;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    ex[j] = lane + kWave * j < E ? exp(static_cast<double>(val[j]) - rmax) : 0.0;
+  for (int j = 0; j < NX; ++j) {
+    ex[j] = lane + kWave * j < E ? exp(static_cast<double>(row.val[j]) - rmax) : 0.0;
     part += ex[j];
   }
   const double den = wave_sum_f64(part);
@@ -215,7 +216,7 @@ __global__ __launch_bounds__(TK_WAVES * kWave) void count_rule_kernel(
   if (rule == REFLEX_RULE_THRESHOLD) {
     int c = 0;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) c += (lane + kWave * j < E && ex[j] / den > thr) ? 1 : 0;
+    for (int j = 0; j < NX; ++j) c += (lane + kWave * j < E && ex[j] / den > thr) ? 1 : 0;
     n = wave_sum_i32(c);
   } else {
     n = k_max;
@@ -223,16 +224,16 @@ __global__ __launch_bounds__(TK_WAVES * kWave) void count_rule_kernel(
     for (int j = 0; j < k_max; ++j) {
       uint64_t b = key[0];
 #pragma unroll
-      for (int x = 1; x < 4; ++x) b = key[x] > b ? key[x] : b;
+      for (int x = 1; x < NX; ++x) b = key[x] > b ? key[x] : b;
       b = wave_max_u64(b);
       const int e = 0xffff - static_cast<int>(b & 0xffffu);
       const int slot = e >> 6;
       double mine = 0.0;
 #pragma unroll
-      for (int x = 0; x < 4; ++x) mine = x == slot ? ex[x] : mine;
+      for (int x = 0; x < NX; ++x) mine = x == slot ? ex[x] : mine;
       const double m = __shfl(mine, e & 63, kWave);
 #pragma unroll
-      for (int x = 0; x < 4; ++x)        // consume the winner (static indices: registers)
+      for (int x = 0; x < NX; ++x)        // consume the winner (static indices: registers)
         key[x] = ((e & 63) == lane && x == slot) ? 0 : key[x];
       cum += m / den;
       if (cum >= thr) {
@@ -546,7 +547,8 @@ __global__ __launch_bounds__(PS_THREADS) void perm_small_kernel(
 // ------------------------------------------------------------------------------------
 // Pair offsets, TopK and (for small layers) the permutation in one launch.  Workgroup
 // b owns tokens 16 b .. 16 b + 15, one wave each: it sums the counts of all earlier
-// tokens itself (no separate scan launch), scans its own 16, writes pair_offsets and
+// tokens itself (no separate scan launch; k NULL: every count is k_max, and k_out, if
+// given, receives them), scans its own 16, writes pair_offsets and
 // runs TopK.  With `done` given, it also ranks each of its pairs among the workgroup's
 // pairs of the same expert (an LDS bit mask of the tokens that chose each expert),
 // keeps (token, rank) in pair_to_sorted and its per-expert counts in hist[b][.]; the
@@ -566,7 +568,7 @@ template <int NX, bool SORT>
 __global__ __launch_bounds__(RF_WAVES * kWave) void route_fused_kernel(
     const float* __restrict__ logits, int n_parts, size_t part_stride,
     const float* __restrict__ bias, float* __restrict__ logits_out,
-    const int32_t* __restrict__ k, int T, int E, int k_max,
+    const int32_t* __restrict__ k, int32_t* __restrict__ k_out, int T, int E, int k_max,
     int norm_topk, int32_t* __restrict__ pair_offsets, int32_t* __restrict__ pair_expert,
     float* __restrict__ pair_weight, int32_t* __restrict__ pairs_out, int32_t* __restrict__ done,
     int32_t* __restrict__ hist, int32_t* __restrict__ expert_offsets,
@@ -586,11 +588,16 @@ __global__ __launch_bounds__(RF_WAVES * kWave) void route_fused_kernel(
     for (int j = 0; j < NX; ++j)
       if (lane + kWave * j < E) logits_out[static_cast<size_t>(i) * E + lane + kWave * j] = row.val[j];
   }
-  int part = 0;     // (unrolled so that several count loads are in flight at once)
-#pragma unroll 8
-  for (int t = tid; t < t0; t += RF_WAVES * kWave) part += clamp_count(k[t], k_max);
-  part = wave_sum_i32(part);
-  const int ki = i < T ? clamp_count(k[i], k_max) : 0;
+  int part = 0, ki = i < T ? k_max : 0;
+  if (k != nullptr) {
+#pragma unroll 8     // several count loads in flight at once
+    for (int t = tid; t < t0; t += RF_WAVES * kWave) part += clamp_count(k[t], k_max);
+    part = wave_sum_i32(part);
+    ki = i < T ? clamp_count(k[i], k_max) : 0;
+  } else {
+    part = wv == 0 ? t0 * k_max : 0;
+    if (k_out != nullptr && i < T && lane == 0) k_out[i] = k_max;
+  }
   if (lane == 0) {
     s_before[wv] = part;
     s_cnt[wv] = ki;
@@ -809,15 +816,23 @@ __global__ __launch_bounds__(256) void block_scatter_kernel(
 
 }  // namespace
 
-int launch_count_rule(const float* logits, int T, int E, int rule, float threshold, int k_min,
+int launch_count_rule(const float* logits, int n_parts, size_t part_stride, const float* bias,
+                      float* finished, int T, int E, int rule, float threshold, int k_min,
                       int k_max, int32_t* k_out, int32_t* pairs_out, hipStream_t s) {
   if (pairs_out != nullptr) {
     const int rc = launch_fill_i32(pairs_out, 0, 1, s);
     if (rc != REFLEX_OK) return rc;
   }
-  hipLaunchKernelGGL(count_rule_kernel, dim3((T + TK_WAVES - 1) / TK_WAVES), dim3(TK_WAVES * kWave),
-                     0, s, logits, T, E, rule, static_cast<double>(threshold), k_min, k_max, k_out,
-                     pairs_out);
+  auto* kernel = &count_rule_kernel<4>;
+  switch (topk_slots(E)) {
+    case 1: kernel = &count_rule_kernel<1>; break;
+    case 2: kernel = &count_rule_kernel<2>; break;
+    case 3: kernel = &count_rule_kernel<3>; break;
+    default: break;
+  }
+  hipLaunchKernelGGL(kernel, dim3((T + TK_WAVES - 1) / TK_WAVES), dim3(TK_WAVES * kWave), 0, s, logits,
+                     n_parts, part_stride, bias, finished, T, E, rule, static_cast<double>(threshold),
+                     k_min, k_max, k_out, pairs_out);
   return launch_status();
 }
 
@@ -865,8 +880,8 @@ int launch_block_sort(const int32_t* pair_offsets, const int32_t* pair_expert, i
 }
 
 int launch_route_fused(const float* logits, int n_parts, size_t part_stride, const float* bias,
-                       float* logits_out, const int32_t* k, int T, int E, int k_max,
-                       int norm_topk, int32_t* pair_offsets, int32_t* pair_expert,
+                       float* logits_out, const int32_t* k, int32_t* k_out, int T, int E,
+                       int k_max, int norm_topk, int32_t* pair_offsets, int32_t* pair_expert,
                        float* pair_weight, int32_t* pairs_out, int32_t* done, int32_t* hist,
                        int32_t* expert_offsets, int32_t* sorted_token, int32_t* pair_to_sorted,
                        hipStream_t s) {
@@ -879,8 +894,8 @@ int launch_route_fused(const float* logits, int n_parts, size_t part_stride, con
     default: break;
   }
   hipLaunchKernelGGL(kernel, dim3((T + RF_WAVES - 1) / RF_WAVES), dim3(RF_WAVES * kWave), 0, s, logits,
-                     n_parts, part_stride, bias, logits_out, k, T, E, k_max, norm_topk, pair_offsets, pair_expert, pair_weight, pairs_out, done,
-                     hist, expert_offsets, sorted_token, pair_to_sorted);
+                     n_parts, part_stride, bias, logits_out, k, k_out, T, E, k_max, norm_topk, pair_offsets,
+                     pair_expert, pair_weight, pairs_out, done, hist, expert_offsets, sorted_token, pair_to_sorted);
   return launch_status();
 }
 
