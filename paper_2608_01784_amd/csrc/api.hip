@@ -218,7 +218,7 @@ bool make_layout(int T, int E, int d, int f, int fs, int kcap, Layout& L) {
     return at;
   };
   // scores, or on the split-K router paths their per-slice partials
-  const int parts = std::max(front_fits(T, d) ? front_slices(d) : 1, router_slices(T, d, E));
+  const int parts = std::max(front_fits(T, d, E) ? front_slices(d) : 1, router_slices(T, d, E));
   L.logits = take(sizeof(float) * static_cast<size_t>(T) * E * parts);
   L.k = take(sizeof(int32_t) * static_cast<size_t>(T));
   L.done = take(sizeof(int32_t));
@@ -519,19 +519,23 @@ static int moe_forward_impl(const reflex_moe_args* a, void* ws, size_t ws_bytes,
   const float* scores = parts;
   int n_parts = 1;
   bool partial = true;      // the partials are to be added yet, and the bias
-  if (front_fits(T, d)) {
-    // small layers: score tiles over K slices, and the REFLEX counts beside them
+  BudgetArgs counts{};
+  if (budget)
+    counts = BudgetArgs{a->block_idx, a->masked, a->hist_len, a->conf_prev1, a->conf_prev2,
+                        a->seq_offsets, a->active_block, a->B, a->params, kb};
+  if (front_fits(T, d, E)) {
+    // score tiles over K slices, and the REFLEX counts beside them
     n_parts = front_slices(d);
-    RFX_TRY(launch_front(a->h, a->w_router, parts, T, d, E, a->block_idx, a->masked, a->hist_len,
-                         a->conf_prev1, a->conf_prev2, a->seq_offsets, a->active_block,
-                         budget ? a->B : 0, a->params, kb, s, done));
+    RFX_TRY(launch_front(a->h, a->w_router, parts, T, d, E, counts, s, done));
     if (budget) k = kb;
-  } else if ((n_parts = router_slices(T, d, E)) > 1) {
-    RFX_TRY(launch_router(a->h, a->w_router, a->router_bias, parts, T, d, E, s, done, n_parts));
   } else {
-    scores = logits;
-    partial = false;
-    RFX_TRY(launch_router(a->h, a->w_router, a->router_bias, logits, T, d, E, s, done));
+    n_parts = router_slices(T, d, E);
+    partial = n_parts > 1;
+    if (!partial) scores = logits;
+    const bool beside = budget && router_takes_counts(T, d, E, a->B);
+    RFX_TRY(launch_router(a->h, a->w_router, a->router_bias, partial ? parts : logits, T, d, E, s, done,
+                          n_parts, beside ? &counts : nullptr));
+    if (beside) k = kb;
   }
   const float* part_bias = partial ? a->router_bias : nullptr;
   float* scores_out = partial ? a->logits_out : nullptr;

@@ -13,7 +13,8 @@ __global__ __launch_bounds__(BG_KERNEL_THREADS) void budget_kernel(
     const float* __restrict__ c2, const int32_t* __restrict__ seq_offsets,
     const int32_t* __restrict__ active_block, int T, BudgetConsts p,
     int32_t* __restrict__ k_out, int32_t* __restrict__ pairs_out, double* __restrict__ fps_out) {
-  budget_sequence<BG_KERNEL_THREADS>(blockIdx.x, block_idx, masked, hist_len, c1, c2, seq_offsets,
+  __shared__ BudgetLds lds;
+  budget_sequence<BG_KERNEL_THREADS>(lds, blockIdx.x, block_idx, masked, hist_len, c1, c2, seq_offsets,
                                      active_block, T, p, k_out, pairs_out, fps_out);
 }
 

@@ -3,7 +3,8 @@
 // (Section 4.2, Eq. (5)) followed by Frontier-Guided Expert Reallocation
 // (Section 4.3, Eqs. (6)-(9)) and the count bounds of Eq. (3).
 //
-// Device code shared by the budget kernel and the fused router + budget kernel.
+// Device code shared by the budget kernel and the router kernels that compute the counts
+// beside the scores.
 //
 // One workgroup per sequence.  The ranking key of every candidate (a masked
 // active-block token with confidence history) is evaluated in fp64 with the
@@ -88,10 +89,19 @@ __device__ __forceinline__ int block_sum(int v, int* red) {
   return s;
 }
 
+// The LDS of one sequence's workgroup (a parameter, so that a kernel can lay it over memory
+// its other workgroups use).
+struct BudgetLds {
+  double key[BG_CHUNK];
+  int idx[BG_CHUNK];
+  int off[BG_CHUNK / kWave + 1];
+  int red[16];
+};
+
 // Counts of sequence s by a workgroup of NT threads.
 template <int NT>
 __device__ __forceinline__ void budget_sequence(
-    int s, const int32_t* __restrict__ block_idx, const uint8_t* __restrict__ masked,
+    BudgetLds& lds, int s, const int32_t* __restrict__ block_idx, const uint8_t* __restrict__ masked,
     const int8_t* __restrict__ hist_len, const float* __restrict__ c1,
     const float* __restrict__ c2, const int32_t* __restrict__ seq_offsets,
     const int32_t* __restrict__ active_block, int T, const BudgetConsts& p,
@@ -99,10 +109,11 @@ __device__ __forceinline__ void budget_sequence(
   constexpr int BG_THREADS = NT;
   constexpr int BG_PER_THREAD = BG_CHUNK / NT;
   constexpr int NW = BG_THREADS / kWave;
-  __shared__ double s_key[BG_CHUNK];
-  __shared__ int s_idx[BG_CHUNK];
-  __shared__ int s_off[BG_PER_THREAD * NW + 1];
-  __shared__ int s_red[NW];
+  static_assert(NW <= 16, "wave sums");
+  double* const s_key = lds.key;
+  int* const s_idx = lds.idx;
+  int* const s_off = lds.off;
+  int* const s_red = lds.red;
 
   int lo = seq_offsets[s], hi = seq_offsets[s + 1];
   lo = lo < 0 ? 0 : (lo > T ? T : lo);

@@ -152,14 +152,30 @@ RFX_DEVICE int clamp_count(int k, int k_max) { return k < 0 ? 0 : (k > k_max ? k
 // Each returns REFLEX_OK or REFLEX_ERR_LAUNCH.  Arguments are already validated.
 namespace rfx {
 
+// The token state and parameters of the REFLEX counts (reflex_assign_budget), for launches
+// that compute them beside the scores.  B = 0: no counts.
+struct BudgetArgs {
+  const int32_t* block_idx;
+  const uint8_t* masked;
+  const int8_t* hist_len;
+  const float *c1, *c2;
+  const int32_t *seq_offsets, *active_block;
+  int B;
+  reflex_alloc_params params;
+  int32_t* k_out;
+};
+
 // zero_word (nullable): set to 0 by the launch (the counter the fused route kernel that
 // follows in the same forward expects to find at zero).  n_slices > 1 (only a value of
 // router_slices(T, d, E)): logits receives n_slices fp32 partial score arrays [T, E]
 // without the bias, slice s covering d columns [s d/n, (s+1) d/n); a score is the
-// partials added in slice order, plus the bias.
+// partials added in slice order, plus the bias.  Where router_takes_counts(T, d, E, B), the
+// launch also computes the counts of `budget` (nullable), B sequences.
+bool router_takes_counts(int T, int d, int E, int B);
 int router_slices(int T, int d, int E);
 int launch_router(const uint16_t* h, const float* w, const float* bias, float* logits, int T,
-                  int d, int E, hipStream_t s, int32_t* zero_word = nullptr, int n_slices = 1);
+                  int d, int E, hipStream_t s, int32_t* zero_word = nullptr, int n_slices = 1,
+                  const BudgetArgs* budget = nullptr);
 
 // pairs_out may be NULL (the fused forward takes P from the count scan instead).
 int launch_budget(const int32_t* block_idx, const uint8_t* masked, const int8_t* hist_len,
@@ -169,18 +185,14 @@ int launch_budget(const int32_t* block_idx, const uint8_t* masked, const int8_t*
 
 int launch_fill_i32(int32_t* dst, int32_t value, int n, hipStream_t s);
 
-// Router scores and REFLEX counts (B = 0: the scores alone) in one launch; only for shapes
-// where front_fits().
+// Router scores and the counts of `budget` in one launch; only for shapes where front_fits().
 // The scores come out as front_slices(d) fp32 partials without the bias, parts[s][T][E]
 // (slice s covers d columns [256 s, 256 s + 256)); a score is the partials added in
 // slice order, plus the bias.
-bool front_fits(int T, int d);
+bool front_fits(int T, int d, int E);
 int front_slices(int d);
 int launch_front(const uint16_t* h, const float* w, float* parts, int T, int d, int E,
-                 const int32_t* block_idx, const uint8_t* masked, const int8_t* hist_len,
-                 const float* c1, const float* c2, const int32_t* seq_offsets,
-                 const int32_t* active_block, int B, const reflex_alloc_params& p, int32_t* k_out,
-                 hipStream_t s, int32_t* zero_word = nullptr);
+                 const BudgetArgs& budget, hipStream_t s, int32_t* zero_word = nullptr);
 
 // One forward's commitment and state bookkeeping, one workgroup per sequence.
 int launch_advance_state(const float* conf_t, const int32_t* block_idx, const int32_t* seq_offsets,

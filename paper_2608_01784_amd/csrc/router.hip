@@ -1,5 +1,6 @@
 // Router scores r = h W_r^T (+ bias), Section 3.2: the launch (the tile code and its
 // description are in router_impl.h).
+#include "budget_impl.h"
 #include "router_impl.h"
 
 namespace rfx {
@@ -54,30 +55,53 @@ __device__ __forceinline__ void rb_wait(int pending) {
   }
 }
 
-template <int TM, int S>
+// BUDGET: the grid's first budget_z planes compute the counts of one sequence per workgroup
+// (independent work, hidden behind the scores instead of 7 us ahead of them), the others the
+// scores.
+template <int TM, int S, bool BUDGET>
 __global__ __launch_bounds__(RB_THREADS) void router_big_kernel(const uint16_t* __restrict__ h,
                                                                 const float* __restrict__ w,
                                                                 const float* __restrict__ bias,
                                                                 float* __restrict__ logits, int T,
                                                                 int d, int E,
                                                                 int32_t* __restrict__ zero_word,
-                                                                int n_slices) {
+                                                                int n_slices, int budget_z,
+                                                                BudgetArgs a, BudgetConsts p) {
   // n_slices > 1: this workgroup covers d columns [ks kd, ks kd + kd), kd = d / n_slices,
-  // ks = blockIdx.z, and writes the partial scores (no bias) to logits + ks T E
+  // ks its plane, and writes the partial scores (no bias) to logits + ks T E
   constexpr int TB = TM / 16;                          // token blocks per wave
   constexpr int H_ELEMS = TM * RB_BK;                  // bf16 per h slice
   constexpr int W_ELEMS = RB_TE * RB_BK;               // fp32 per W slice
   constexpr int H_OPS = TM / 8 / 4;                    // 1 KB copies per wave (8 h rows each)
   constexpr int W_OPS = RB_TE / 4 / 4;                 // (4 W rows each)
   static_assert(S >= 2 && S <= 4, "ring depth");
-  __shared__ __attribute__((aligned(16))) uint16_t s_h[S][H_ELEMS];
-  __shared__ __attribute__((aligned(16))) float s_w[S][W_ELEMS];
+  struct Ring {
+    uint16_t h[S][H_ELEMS];
+    float w[S][W_ELEMS];
+  };
+  __shared__ __attribute__((aligned(16))) char s_mem[sizeof(Ring)];
+  Ring& ring = *reinterpret_cast<Ring*>(s_mem);
+  auto& s_h = ring.h;
+  auto& s_w = ring.w;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if constexpr (BUDGET) {
+    static_assert(sizeof(BudgetLds) <= sizeof(Ring), "the counts' LDS lies over the rings");
+    const int z = blockIdx.z;
+    if (z < budget_z) {
+      const int b = (z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+      if (b < a.B)
+        budget_sequence<RB_THREADS>(*reinterpret_cast<BudgetLds*>(s_mem), b, a.block_idx, a.masked,
+                                    a.hist_len, a.c1, a.c2, a.seq_offsets, a.active_block, T, p,
+                                    a.k_out, nullptr, nullptr);
+      return;
+    }
+  }
+  const int ks = blockIdx.z - (BUDGET ? budget_z : 0);
   const int t0 = blockIdx.x * TM, e0 = blockIdx.y * RB_TE;
-  const int kd = d / n_slices, kbase = blockIdx.z * kd;
+  const int kd = d / n_slices, kbase = ks * kd;
   const int nk = kd / RB_BK;
-  if (zero_word != nullptr && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && tid == 0)
+  if (zero_word != nullptr && blockIdx.x == 0 && blockIdx.y == 0 && ks == 0 && tid == 0)
     *zero_word = 0;
 
   // copy sources: lane L of an h op fills row 8q + L/8, slot L%8; of a W op row 4q + L/16,
@@ -156,7 +180,7 @@ __global__ __launch_bounds__(RB_THREADS) void router_big_kernel(const uint16_t* 
   const int e = e0 + 16 * wv + (lane & 15);
   if (e < E) {
     const float be = (bias && n_slices == 1) ? bias[e] : 0.0f;
-    float* out = logits + static_cast<size_t>(blockIdx.z) * T * E;
+    float* out = logits + static_cast<size_t>(ks) * T * E;
 #pragma unroll
     for (int b = 0; b < TB; ++b)
 #pragma unroll
@@ -169,46 +193,58 @@ __global__ __launch_bounds__(RB_THREADS) void router_big_kernel(const uint16_t* 
 
 }  // namespace
 
-// K slices of the split-K router for T >= 4096 (1: finished scores).  The 128-token x
+static long big_tiles(int T, int E) {
+  return static_cast<long>((T + 127) / 128) * ((E + RB_TE - 1) / RB_TE);
+}
+
+// K slices of the split-K router (1: finished scores).  The 128-token x
 // 64-expert LDS-staged tiles re-read neither operand much (h once per 64 experts, W_r
 // once per 128 tokens), so where they are too few to fill the GPU the K range is split
 // instead of shrinking the tiles: up to ~512 workgroups (two fit a CU), slices of at
 // least 256 columns.
 int router_slices(int T, int d, int E) {
-  if (T < 4096 || d % RB_BK != 0) return 1;
-  const long tiles = static_cast<long>((T + 127) / 128) * ((E + RB_TE - 1) / RB_TE);
+  if ((T < 4096 && static_cast<long>(T) * E < (1L << 17)) || d % RB_BK != 0) return 1;
+  const long tiles = big_tiles(T, E);
   int ns = 1;
   while (tiles * ns * 2 <= 512 && d % (2 * ns * 256) == 0) ns *= 2;
   return ns;
 }
 
+bool router_takes_counts(int T, int d, int E, int B) {
+  return (router_slices(T, d, E) > 1 || big_tiles(T, E) >= 512) && B / big_tiles(T, E) < 32768;
+}
+
 int launch_router(const uint16_t* h, const float* w, const float* bias, float* logits, int T,
-                  int d, int E, hipStream_t s, int32_t* zero_word, int n_slices) {
+                  int d, int E, hipStream_t s, int32_t* zero_word, int n_slices,
+                  const BudgetArgs* budget) {
   // A workgroup's loads all pass through one CU, so tiles are sized to spread the
-  // traffic over many CUs: small T uses 16 x 16 tiles with K split over 16 waves.  For
-  // T >= 4096 the split-K path (n_slices > 1, partial scores for the caller to add) runs
-  // 128 x 64 tiles over a slice of d each.  With finished scores requested: 128 x 64
+  // traffic over many CUs: small T uses 16 x 16 tiles with K split over 16 waves.  The
+  // split-K path (n_slices > 1, partial scores for the caller to add) runs 128 x 64 tiles
+  // over a slice of d each.  With finished scores requested: 128 x 64
   // tiles where that gives 512 or more (T = 16384, E = 256), else 32 x 64 tiles (T = 4096,
   // E = 256: 33 us against 39 us for 64 x 64 register tiles), and with at most 64 experts
   // the register kernel with 32-token tiles and K split over 8 waves (T = 8192, E = 64:
   // 29 us against 34 us and 38 us for the LDS kernel and 64 x 64 register tiles; all
   // measured).
-  if (n_slices > 1) {
-    hipLaunchKernelGGL((router_big_kernel<128, 2>),
-                       dim3((T + 127) / 128, (E + RB_TE - 1) / RB_TE, n_slices), dim3(RB_THREADS), 0,
-                       s, h, w, bias, logits, T, d, E, zero_word, n_slices);
-    return launch_status();
-  }
-  const long big_tiles = static_cast<long>((T + 127) / 128) * ((E + RB_TE - 1) / RB_TE);
-  if (big_tiles >= 512) {
-    hipLaunchKernelGGL((router_big_kernel<128, 2>), dim3((T + 127) / 128, (E + RB_TE - 1) / RB_TE),
-                       dim3(RB_THREADS), 0, s, h, w, bias, logits, T, d, E, zero_word, 1);
+  if (n_slices > 1 || big_tiles(T, E) >= 512) {
+    const int gx = (T + 127) / 128, gy = (E + RB_TE - 1) / RB_TE;
+    if (budget != nullptr && budget->B > 0) {
+      const int bz = (budget->B + gx * gy - 1) / (gx * gy);
+      hipLaunchKernelGGL((router_big_kernel<128, 2, true>), dim3(gx, gy, n_slices + bz),
+                         dim3(RB_THREADS), 0, s, h, w, bias, logits, T, d, E, zero_word, n_slices, bz,
+                         *budget, budget_consts(budget->params));
+    } else {
+      hipLaunchKernelGGL((router_big_kernel<128, 2, false>), dim3(gx, gy, n_slices), dim3(RB_THREADS),
+                         0, s, h, w, bias, logits, T, d, E, zero_word, n_slices, 0, BudgetArgs{},
+                         BudgetConsts{});
+    }
   } else if (T >= 4096 && E <= 64 && d % (RT_TK * 8) == 0) {
     hipLaunchKernelGGL((router_mfma_kernel<32, 4, 8, 2>), dim3((T + 31) / 32, (E + 63) / 64),
                        dim3(512), 0, s, h, w, bias, logits, T, d, E, zero_word);
   } else if (T >= 4096) {
-    hipLaunchKernelGGL((router_big_kernel<32, 2>), dim3((T + 31) / 32, (E + RB_TE - 1) / RB_TE),
-                       dim3(RB_THREADS), 0, s, h, w, bias, logits, T, d, E, zero_word, 1);
+    hipLaunchKernelGGL((router_big_kernel<32, 2, false>), dim3((T + 31) / 32, (E + RB_TE - 1) / RB_TE),
+                       dim3(RB_THREADS), 0, s, h, w, bias, logits, T, d, E, zero_word, 1, 0, BudgetArgs{},
+                       BudgetConsts{});
   } else if (d % (RT_TK * 16) == 0) {
     hipLaunchKernelGGL((router_mfma_kernel<16, 1, 16, 4>), dim3((T + 15) / 16, (E + 15) / 16),
                        dim3(1024), 0, s, h, w, bias, logits, T, d, E, zero_word);
