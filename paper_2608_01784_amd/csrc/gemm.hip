@@ -152,12 +152,12 @@ __device__ __forceinline__ void store_block(const f32x16_t& g, const f32x16_t& u
 // us here; LLaDA2.0-mini shape at 164 rows 500 against 388 us.)
 //
 // Two waves share each SIMD.  The waves form 2 (pair rows) x 4 (weight rows): wave
-// (wm, wn) multiplies pair rows 128 wm .. 128 wm + 127 (four 32-row blocks) by 64
+// (wm, wn) multiplies the 32-row pair blocks wm, wm + 2, wm + 4, wm + 6 by 64
 // weight rows (UP: the 32 gate rows and the 32 matching up rows of activation columns
 // n0 + 32 wn ..; DOWN: weight rows 64 wn ..).  Waves w and w + 4 share a SIMD, so each
-// SIMD holds one wave of each row half: an expert's last tile, whose rows end early,
-// shortens the MFMA stream of all four SIMDs alike (row blocks past the expert's end
-// are skipped), instead of idling some SIMDs while the others run a full tile.  The K
+// SIMD holds one wave of each wm: an expert's last tile, whose rows end early, shortens
+// the MFMA stream of all four SIMDs, and of both their waves, alike (row blocks past the
+// expert's end are skipped), instead of idling some while the others run a full tile.  The K
 // loop is instantiated per count of active row blocks, so the common full tile runs
 // straight-line code with no per-block branches.  Every wave issues its share of the
 // global->LDS copies of the next input-row slice and of the weight slice two steps
@@ -237,7 +237,7 @@ __global__ __launch_bounds__(Geometry<S>::THREADS) void swiglu_gemm_kernel(
   // workgroup into LDS (scratch: the rings are empty until the first copies; every wave
   // reading them from memory would queue up at the same few cache lines), the prefix is four
   // wave scans that every wave does for itself.
-  int toff_r[4], eo_r[4], eo_E = 0, m_total = 0;
+  int toff_r[4], eo_r[4], eo_E = 0, m_total = 0, bm_log = __builtin_ctz(TL_BM);
   {
     int* s_eo = reinterpret_cast<int*>(smem);
     for (int e = tid; e <= E; e += G::THREADS) s_eo[e] = E > 0 ? expert_offsets[e] : 0;
@@ -250,13 +250,44 @@ __global__ __launch_bounds__(Geometry<S>::THREADS) void swiglu_gemm_kernel(
       n[q] = s_eo[e < E ? e + 1 : E] - eo_r[q];
     }
     eo_E = __builtin_amdgcn_readfirstlane(s_eo[E]);
+    // Rows per tile (2^bm_log): 256-row tiles are cut to 128 rows where few, far larger experts
+    // would outlast all others by a tile: the largest has over four times the mean of the
+    // experts with pairs, and the cut adds at most a quarter to the tiles (Zipf-skewed
+    // experts, forward at T = 256 / 512 / 1024: 164 / 159 / 171 us uncut, 155 / 146 / 159 cut;
+    // T = 2048, where the cut adds more: 200 us uncut, 215 cut).  Cutting evenly filled experts
+    // only reads their weights twice (LLaDA-MoE, 110 rows each: 200 us uncut, 222 cut).  The
+    // always-on expert by itself: up to 4096 rows, to have more tiles beside the routing
+    // (LLaDA2.0-mini, T = 4096: forward 422 us uncut, 415 cut; T = 8192: 508 and 541).
+    auto prefix = [&]() {
+      m_total = 0;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int tiles = n[q] < 0 ? 0 : (n[q] + TL_BM - 1) / TL_BM;
-      const int incl = wave_inclusive_scan_i32(tiles, lane);
-      // (scaled to tiles; lanes past E: never at or before a tile)
-      toff_r[q] = lane + 64 * q < E ? (m_total + incl - tiles) * n_tiles : INT32_MAX;
-      m_total += __builtin_amdgcn_readlane(incl, 63);
+      for (int q = 0; q < 4; ++q) {
+        const int tiles = n[q] < 0 ? 0 : (n[q] + (1 << bm_log) - 1) >> bm_log;
+        const int incl = wave_inclusive_scan_i32(tiles, lane);
+        // (scaled to tiles; lanes past E: never at or before a tile)
+        toff_r[q] = lane + 64 * q < E ? (m_total + incl - tiles) * n_tiles : INT32_MAX;
+        m_total += __builtin_amdgcn_readlane(incl, 63);
+      }
+    };
+    prefix();
+    if constexpr (TL_BM == 256) {
+      int used = 0;
+      uint64_t far = 0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) used += __popcll(__ballot(n[q] > 0));
+      const float mean4 = 4.0f * static_cast<float>(eo_E) / static_cast<float>(max(used, 1));
+#pragma unroll
+      for (int q = 0; q < 4; ++q) far |= __ballot(static_cast<float>(n[q]) > mean4);
+      if (far != 0) {
+        int more = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) more += n[q] <= 0 ? 0 : ((n[q] + 127) >> 7) - ((n[q] + 255) >> 8);
+        if (__builtin_amdgcn_readfirstlane(wave_sum_i32(more)) <= m_total / 4) {
+          bm_log = 7;
+          prefix();
+        }
+      }
+      if (E == 0 && sh_rows <= 4096) bm_log = 7;
     }
     __syncthreads();     // all scratch reads done before the first copies land
   }
@@ -291,8 +322,8 @@ __global__ __launch_bounds__(Geometry<S>::THREADS) void swiglu_gemm_kernel(
       split(L, m, n);
       t.expert = E;
       t.n0 = n * BN;
-      t.row0 = sh_row0 + m * TL_BM;
-      t.row_end = sh_row0 + sh_rows;
+      t.row0 = sh_row0 + (m << bm_log);
+      t.row_end = min(sh_row0 + sh_rows, t.row0 + (1 << bm_log));
       t.rot = n % nk;
       return t;
     }
@@ -305,8 +336,8 @@ __global__ __launch_bounds__(Geometry<S>::THREADS) void swiglu_gemm_kernel(
     const int er1 = lo + 1 < E ? table_at(eo_r, lo + 1) : eo_E;
     t.expert = lo;
     t.n0 = n * BN;
-    t.row0 = er0 + m * TL_BM;
-    t.row_end = er1 < out_rows ? er1 : out_rows;
+    t.row0 = er0 + (m << bm_log);
+    t.row_end = min(min(er1, out_rows), t.row0 + (1 << bm_log));
     if (t.row0 < 0 || t.row0 >= t.row_end) t.row_end = t.row0;   // inconsistent offsets: no rows
     // K rotation: tile (M tile m of expert e, N tile n) walks its K slices starting at
     // slice n mod nk (down) or (n mod 2 + 5 e) mod nk (up).  The tiles sharing an input-row
@@ -332,7 +363,7 @@ __global__ __launch_bounds__(Geometry<S>::THREADS) void swiglu_gemm_kernel(
   const int xcd = blockIdx.x % GM_XCDS;
   const int per_xcd = gridDim.x / GM_XCDS;
   const int j0 = blockIdx.x / GM_XCDS;
-  const int sh_tiles = (sh_rows + TL_BM - 1) / TL_BM * n_tiles;
+  const int sh_tiles = ((sh_rows + (1 << bm_log) - 1) >> bm_log) * n_tiles;
   const int sh_mine = (max(sh_tiles - xcd, 0) + GM_XCDS - 1) / GM_XCDS;
   const int chunk = (routed_tiles + GM_XCDS - 1) / GM_XCDS;
   const int r_begin = xcd * chunk, r_mine = max(min(routed_tiles - r_begin, chunk), 0);
@@ -514,7 +545,7 @@ __global__ __launch_bounds__(Geometry<S>::THREADS) void swiglu_gemm_kernel(
         b_rsrc, (__attribute__((address_space(3))) void*)(Bs_ + (TL_B_OPS * wave + j) * 512), 16,
         voff, 0, 0, kDmaPolicy);
   };
-  // ---- multiply: pair blocks 32 MI wm + 32 i, weight blocks b_row[j]
+  // ---- multiply: pair blocks WM i + wm of the tile, weight blocks b_row[j]
   const int b_row[TL_NJ] = {UP ? 32 * wn : 64 * wn, UP ? G::BROWS / 2 + 32 * wn : 64 * wn + 32};
   const int frow = lane & 31, fsel = lane >> 5, fx = (frow / TL_RG) % TL_CH;
   f32x16_t acc[TL_MI][TL_NJ];
@@ -601,7 +632,7 @@ __global__ __launch_bounds__(Geometry<S>::THREADS) void swiglu_gemm_kernel(
 #pragma unroll
           for (int i = 0; i < NB; ++i)
             af[buf][i] =
-                *reinterpret_cast<const bf16x8_t*>(As + (32 * TL_MI * wm + 32 * i + frow) * TL_BK + slot);
+                *reinterpret_cast<const bf16x8_t*>(As + (32 * (S::WM * i + wm) + frow) * TL_BK + slot);
 #pragma unroll
           for (int j = 0; j < TL_NJ; ++j)
             bfr[buf][j] = *reinterpret_cast<const bf16x8_t*>(Bs + (b_row[j] + frow) * TL_BK + slot);
@@ -657,10 +688,10 @@ __global__ __launch_bounds__(Geometry<S>::THREADS) void swiglu_gemm_kernel(
         set_b(next_t);
       }
     }
-    // pair blocks of this wave's 32 MI rows that hold pairs (wave-uniform)
-    int rows = t.row_end - t.row0 - 32 * TL_MI * wm;
-    rows = rows < 0 || wm >= S::WM ? 0 : (rows > 32 * TL_MI ? 32 * TL_MI : rows);
-    const int nb = __builtin_amdgcn_readfirstlane((rows + 31) >> 5);
+    // pair blocks of this wave that hold pairs (wave-uniform): blocks wm, wm + WM, .. of the tile
+    const int blocks = (t.row_end - t.row0 + 31) >> 5;
+    const int nb = __builtin_amdgcn_readfirstlane(
+        wm < S::WM ? min(max(blocks - wm + S::WM - 1, 0) / S::WM, TL_MI) : 0);
 #pragma unroll
     for (int i = 0; i < TL_MI; ++i)
 #pragma unroll
@@ -672,12 +703,6 @@ __global__ __launch_bounds__(Geometry<S>::THREADS) void swiglu_gemm_kernel(
       switch (nb) {
         case 4: k_loop(std::integral_constant<int, 4>{}); break;
         case 3: k_loop(std::integral_constant<int, 3>{}); break;
-        case 2: k_loop(std::integral_constant<int, 2>{}); break;
-        case 1: k_loop(std::integral_constant<int, 1>{}); break;
-        default: k_loop(std::integral_constant<int, 0>{}); break;
-      }
-    } else if constexpr (TL_MI == 2) {
-      switch (nb) {
         case 2: k_loop(std::integral_constant<int, 2>{}); break;
         case 1: k_loop(std::integral_constant<int, 1>{}); break;
         default: k_loop(std::integral_constant<int, 0>{}); break;
@@ -697,7 +722,7 @@ __global__ __launch_bounds__(Geometry<S>::THREADS) void swiglu_gemm_kernel(
 #pragma unroll
     for (int i = 0; i < TL_MI; ++i) {
       if (i < nb) {
-        const int rb = t.row0 + 32 * TL_MI * wm + 32 * i;
+        const int rb = t.row0 + 32 * (S::WM * i + wm);
         if (UP) {
           store_block<true>(acc[i][0], acc[i][1], rb, t.n0 + 32 * wn, t.row_end, N_out, out, stage);
         } else {
@@ -714,7 +739,6 @@ __global__ __launch_bounds__(Geometry<S>::THREADS) void swiglu_gemm_kernel(
 }
 // The tile shapes (pair rows x weight rows); the rule between them is at launch_gemm.
 using Tall = Shape<4, 2, 4, 8, 2, 3>;       // 256 x 256, 160 KB of LDS, one workgroup per CU
-using Half = Shape<2, 2, 4, 8, 2, 3>;       // 128 x 256, 128 KB, one per CU
 using Medium = Shape<1, 2, 2, 4, 2, 3>;     // 64 x 128, 64 KB, two per CU
 using Narrow = Shape<1, 1, 1, 4, 3, 3>;     // 32 x 64, 36 KB, four per CU
 
@@ -756,13 +780,7 @@ long capacity_tiles(int cap, int E, int sh_rows, int N) {
   return m * ((N + BN - 1) / BN);
 }
 
-// The tile shape of a launch.  The always-on expert in launches of its own (E = 0, beside the
-// routing) takes 128-row tiles up to T = 2048, whose up GEMM ends with the routing, and
-// 256-row ones above, whose down GEMM then waits for the tail of the routed up GEMM instead
-// of starting together with it (LLaDA2.0-mini shape, forward at T = 1024 / 2048 / 4096 / 8192
-// 354 / 397 / 434 / 546 us with 128-row tiles, 360 / 400 / 426 / 511 with 256-row ones).
-//
-// The routed experts:  An expert has at most as many rows as there are tokens (T), so
+// The tile shape of a launch.  An expert has at most as many rows as there are tokens (T), so
 // up to 32 (64) tokens a 32-row (64-row) tile reads its weights once, as the 256-row tile
 // does, and its finer tiles spread over the CUs more evenly: forward of the LLaDA-MoE shape
 // at T = 1 / 5 / 32 60 / 139 / 162 us with 256-row tiles, 47 / 112 / 158 us with 32-row ones,
@@ -788,14 +806,16 @@ int launch_gemm(const uint16_t* x, const int32_t* gather, const int32_t* eo, int
   if (static_cast<size_t>(x_rows) * static_cast<size_t>(K) >= (size_t(1) << 30)) {
     launch = &launch_gemm_as<UP, Tall, true>;
   } else {
+    // the always-on expert in launches of its own runs beside the routing: 256-row tiles (cut
+    // to 128 rows by the kernel) leave the routing launches more CUs than smaller ones
     const bool alone = E == 0 && T > Geometry<Medium>::BM;
     const bool few = 2 * capacity_tiles<UP, Tall>(cap, E, sh.rows, N) <= cus;
-    if (alone)
-      launch = T <= 2048 ? &launch_gemm_as<UP, Half, false> : launch;
-    else if (T <= Geometry<Narrow>::BM || (few && 4 * capacity_tiles<UP, Medium>(cap, E, sh.rows, N) <= cus))
-      launch = &launch_gemm_as<UP, Narrow, false>;
-    else if (T <= Geometry<Medium>::BM || few)
-      launch = &launch_gemm_as<UP, Medium, false>;
+    if (!alone) {
+      if (T <= Geometry<Narrow>::BM || (few && 4 * capacity_tiles<UP, Medium>(cap, E, sh.rows, N) <= cus))
+        launch = &launch_gemm_as<UP, Narrow, false>;
+      else if (T <= Geometry<Medium>::BM || few)
+        launch = &launch_gemm_as<UP, Medium, false>;
+    }
   }
   return launch(x, gather, eo, E, w0, w1, stride, sh, K, N, x_rows, cap, out, s);
 }

@@ -110,9 +110,10 @@ def test_operands_past_32_bit_offsets(torch, which):
     (24, 64, 12, 128),      # rides, 32-row tiles
     (60, 256, 12, 128),     # rides, 64-row tiles
     (105, 256, 12, 128),    # rides, 256-row tiles
-    (107, 256, 12, 128),    # just past the rule: launches of its own, 128-row tiles
+    (107, 256, 12, 128),    # just past the rule: launches of its own, tiles cut to 128 rows
     (40, 16, 4, 192),       # another width: launches of its own, 64-row tiles
-    (2100, 16, 4, 128),     # launches of its own, 256-row tiles
+    (2100, 16, 4, 128),     # launches of its own, tiles cut to 128 rows
+    (4100, 16, 4, 128),     # launches of its own, 256-row tiles
 ])
 @pytest.mark.parametrize("no_pairs", [False, True])
 def test_always_on_expert(torch, T, E, kmax, fs, no_pairs):
@@ -137,3 +138,61 @@ def test_always_on_expert(torch, T, E, kmax, fs, no_pairs):
     layer_tolerance_check(oracle.bf16_to_f64(bf16_bits(out))[toks], ref,
                           f"always-on expert T={T} E={E} fs={fs} no_pairs={no_pairs}")
     note("ok")
+
+
+@pytest.mark.parametrize("big,rest", [(257, 3), (1000, 10), (129, 30), (300, 128)])
+def test_few_large_experts(torch, big, rest):
+    # 256-row tiles cut to 128 rows where few experts have far more rows than the others
+    # (the first three; in the fourth no expert has four times the mean)
+    from paper_2608_01784_amd import _lib as L
+    rng = np.random.default_rng(big)
+    T, E, d, f = 1100, 192, 256, 128
+    counts = np.full(E, rest)
+    counts[[5, 77]] = [big, max(rest, big // 2 + 1)]
+    counts[100:110] = 0
+    P = int(counts.sum())
+    eo = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    st = rng.integers(0, T, P).astype(np.int32)
+
+    def bf16(shape, scale):
+        return bf16_bits_from_f32((rng.standard_normal(shape) * scale).astype(np.float32))
+
+    h, wg, wu = bf16((T, d), 1.0), bf16((E, f, d), d ** -0.5), bf16((E, f, d), d ** -0.5)
+    wd = bf16((E, d, f), 0.3 * f ** -0.5)
+    y = torch.full((P, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    ws = torch.empty(L.reflex_swiglu_workspace_size(P, E, f), dtype=torch.uint8, device="cuda")
+    L.reflex_grouped_swiglu(to_device(h), to_device(st), to_device(eo), to_device(wg), to_device(wu),
+                            to_device(wd), y, ws)
+    torch.cuda.synchronize()
+    yb = bf16_bits(y)
+    ref = np.concatenate([oracle.swiglu_expert(oracle.bf16_to_f64(h[st[eo[e]:eo[e + 1]]]),
+                                               *(oracle.bf16_to_f64(w[e]) for w in (wg, wu, wd)))
+                          for e in np.flatnonzero(counts)])
+    layer_tolerance_check(oracle.bf16_to_f64(yb), ref, f"experts of {big} and {rest} rows")
+
+
+@pytest.mark.parametrize("T,E,B", [(2048, 64, 1), (512, 256, 300), (520, 256, 2), (16384, 256, 1000),
+                                   (4100, 64, 5)])
+def test_counts_beside_the_scores(torch, T, E, B):
+    # the launch of large score tiles computes the counts of B sequences in its first
+    # workgroups: more sequences than tiles, empty sequences, one sequence of several slices
+    from paper_2608_01784_amd.layer import ExpertWeights, MoELayer, TokenState
+    from gpu_common import oracle_budget
+    w = make_fuzz_workload(400 + B, T=T, d=512 if T < 16384 else 128, E=E, f=64, k_max=8)
+    rng = np.random.default_rng(B)
+    cuts = np.sort(rng.integers(0, T + 1, B - 1)) if B > 1 else np.zeros(0, int)
+    w.seq_offsets = np.concatenate([[0], cuts, [T]]).astype(np.int32)
+    w.active_block = rng.integers(1, 5, B).astype(np.int32)
+    dw = {"w_gate": to_device(w.w_gate()), "w_up": to_device(w.w_up()), "w_down": to_device(w.w_down()),
+          "w_router": to_device(w.w_router()),
+          "router_bias": None if w.router_bias is None else to_device(w.router_bias)}
+    lay = MoELayer(w.T, w.d, ExpertWeights(**dw), w.params)
+    lay.forward(to_device(w.h), TokenState(**state_tensors(w)))
+    torch.cuda.synchronize()
+    assert np.array_equal(lay.k.cpu().numpy(), oracle_budget(w).k)
+    toks = np.unique(np.linspace(0, T - 1, 500).astype(int))
+    ref = oracle.bf16_to_f64(w.h[toks]) @ w.w_router().astype(np.float64).T
+    if w.router_bias is not None:
+        ref = ref + w.router_bias
+    got = lay.logits.cpu().numpy()[toks]
+    assert (np.abs(got - ref).max(1) <= 1e-4 * np.abs(ref).max(1)).all()
