@@ -218,7 +218,7 @@ int launch_topk(const float* logits, const int32_t* k, int T, int E, int k_max, 
 //  - route_fused_sorts(T, E): inside this launch, given hist (route_hist_bytes(T, E) of
 //    scratch) and `done`, a device word the preceding launch set to zero;
 //  - route_block_sorts(T, E): given hist and done NULL, this launch ranks the pairs in
-//    their 16-token blocks (counts expert-major in hist) and launch_block_sort finishes;
+//    their 16-token blocks (counts in hist) and launch_block_sort finishes;
 //  - otherwise hist and done NULL, and launch_permute follows.
 // pairs_out nullable.  The scores are n_parts partials part_stride floats apart, added
 // in order, plus bias (nullable); n_parts = 1 with bias NULL reads finished scores.

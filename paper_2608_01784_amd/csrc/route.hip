@@ -560,7 +560,11 @@ __global__ __launch_bounds__(PS_THREADS) void perm_small_kernel(
 // counter to zero, which is where the launch before this one left it.
 // ------------------------------------------------------------------------------------
 constexpr int RF_WAVES = 16;
-constexpr int RF_HIST_MAX = 16384;       // workgroups x experts held in LDS by the last one
+// Workgroups x experts, one count per thread of the last workgroup: alone it takes as long
+// as the one block-sort launch at 512 counts (route + sort 17.5 us at T = 128, E = 64) and
+// longer above (12544 / 16384 counts, T = 777, E = 256 / T = 4096, E = 64: 24 / 36 us
+// against 18 / 18).
+constexpr int RF_HIST_MAX = RF_WAVES * kWave;
 
 // SORT: this launch sorts the pairs (its last workgroup, above).  Without it the kernel
 // holds none of that step's LDS tables, so two workgroups fit a CU instead of one.
@@ -572,7 +576,7 @@ __global__ __launch_bounds__(RF_WAVES * kWave) void route_fused_kernel(
     int norm_topk, int32_t* __restrict__ pair_offsets, int32_t* __restrict__ pair_expert,
     float* __restrict__ pair_weight, int32_t* __restrict__ pairs_out, int32_t* __restrict__ done,
     int32_t* __restrict__ hist, int32_t* __restrict__ expert_offsets,
-    int32_t* __restrict__ sorted_token, int32_t* __restrict__ pair_to_sorted) {
+    int32_t* __restrict__ sorted_token, int32_t* __restrict__ pair_to_sorted, int block_major) {
   __shared__ int s_before[RF_WAVES], s_cnt[RF_WAVES];
   __shared__ uint32_t s_mask[REFLEX_MAX_EXPERTS];
   __shared__ int s_last;
@@ -623,9 +627,9 @@ __global__ __launch_bounds__(RF_WAVES * kWave) void route_fused_kernel(
   __syncthreads();
   if (my_e >= 0)       // (token, rank among this workgroup's tokens that chose my_e)
     pair_to_sorted[off + lane] = (i << 5) | __popc(s_mask[my_e] & ((1u << wv) - 1u));
-  if (!SORT) {     // the block-sort launches finish: counts expert-major
-    for (int e = tid; e < E; e += RF_WAVES * kWave)
-      hist[static_cast<size_t>(e) * gridDim.x + blockIdx.x] = __popc(s_mask[e]);
+  if (!SORT) {     // the block-sort launches finish
+    const size_t se = block_major ? 1 : gridDim.x, sb = block_major ? E : 1;
+    for (int e = tid; e < E; e += RF_WAVES * kWave) hist[e * se + blockIdx.x * sb] = __popc(s_mask[e]);
     return;
   }
   for (int e = tid; e < E; e += RF_WAVES * kWave)
@@ -648,19 +652,10 @@ __global__ __launch_bounds__(RF_WAVES * kWave) void route_fused_kernel(
   __shared__ int s_part[RF_WAVES][REFLEX_MAX_EXPERTS];
   __shared__ int s_eo[REFLEX_MAX_EXPERTS];
   __shared__ int s_wave[4];
-  constexpr int RF_THREADS = RF_WAVES * kWave;
-  constexpr int RF_TAB_PT = RF_HIST_MAX / RF_THREADS;     // table words per thread, at most
   const int G = gridDim.x, n_tab = G * E;
-  // the whole table's loads in flight at once (a uniform branch skips the unused
-  // slices), then the pair count's, then one wait
-  int hv[RF_TAB_PT];
-#pragma unroll
-  for (int j = 0; j < RF_TAB_PT; ++j)
-    if (j * RF_THREADS < n_tab) hv[j] = hist[min(tid + j * RF_THREADS, n_tab - 1)];
-  const int P = pair_offsets[T];
-#pragma unroll
-  for (int j = 0; j < RF_TAB_PT; ++j)
-    if (j * RF_THREADS < n_tab && tid + j * RF_THREADS < n_tab) s_tab[tid + j * RF_THREADS] = hv[j];
+  const int hv = hist[min(tid, n_tab - 1)];
+  const int P = pair_offsets[T];     // (both loads in flight at once)
+  if (tid < n_tab) s_tab[tid] = hv;
   // the first pass's scatter inputs do not depend on the start rows: their loads go
   // out now and their latency hides behind the scans (a barrier does not wait for them)
   int v[RF_BATCH], ev[RF_BATCH];
@@ -736,16 +731,24 @@ __global__ __launch_bounds__(RF_WAVES * kWave) void route_fused_kernel(
 // ------------------------------------------------------------------------------------
 // Block sort (layers above RF_HIST_MAX counts): the route launch has ranked every pair
 // among its 16-token block's pairs of the same expert (pair_to_sorted = token << 5 |
-// rank) and written the blocks' per-expert counts expert-major, cnt[e][b].  Two
-// launches finish the stable (expert, token) order, with no workgroup walking every
-// pair and no cross-workgroup wait:
+// rank) and written the blocks' per-expert counts.  One or two launches finish the stable
+// (expert, token) order, with no workgroup walking every pair and no cross-workgroup wait.
+// Up to BS_ONE_MAX counts (block-major, cnt[b][e]) one launch: workgroup b sums the whole
+// table, the blocks before its own apart, which gives it the expert bases and its start
+// rows, and sends its pairs to base[e] + start[e][b] + rank.  Latency bounds it (7 us, a
+// launch's own 4.5 included); every workgroup reads the table, which at 16384 counts is 64
+// KB from L2.  Above, counts expert-major, cnt[e][b], and two launches:
 //   column scan: workgroup e turns row e of cnt into start rows (the pairs of expert e
 //   in earlier blocks), in place, and writes the expert's total to tot[e];
 //   scatter: every workgroup scans the E totals into expert bases (workgroup 0 also
 //   writes them as expert_offsets) and sends each pair of its block b to base[e] + start[e][b] + rank.
+// At 32768 counts (T = 2048, E = 256 / T = 8192, E = 64) both take 8 to 11 us; at 65536
+// (T = 4096, E = 256) one launch takes 11.2 us against 9.8, and the forward, whose shared
+// expert runs beside it, 435 against 416.
 // ------------------------------------------------------------------------------------
 constexpr int BS_THREADS = 1024;
 constexpr long BS_MAX_COUNTS = 1L << 20;   // (block, expert) counts the block sort takes
+constexpr long BS_ONE_MAX = 16384;         // ... in one launch
 
 __global__ __launch_bounds__(BS_THREADS) void block_colscan_kernel(int32_t* __restrict__ cnt,
                                                                    int G,
@@ -814,6 +817,85 @@ __global__ __launch_bounds__(256) void block_scatter_kernel(
   }
 }
 
+// The one launch.  Thread: expert tid mod 2^e_log, every n_q-th block; 16 counts in flight.
+__global__ __launch_bounds__(BS_THREADS) void block_sort_kernel(
+    const int32_t* __restrict__ pair_offsets, const int32_t* __restrict__ pair_expert, int T,
+    int cap, int E, int e_log, int G, const int32_t* __restrict__ cnt,
+    int32_t* __restrict__ expert_offsets, int32_t* __restrict__ sorted_token,
+    int32_t* __restrict__ pair_to_sorted) {
+  constexpr int BATCH = 16;
+  __shared__ int s_all[BS_THREADS], s_before[BS_THREADS];
+  __shared__ int s_base[REFLEX_MAX_EXPERTS];
+  __shared__ int s_wave[4];
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int t0 = b * RF_WAVES, t1 = min(T, t0 + RF_WAVES);
+  int p0 = pair_offsets[t0], p1 = pair_offsets[t1];
+  const int e = tid & ((1 << e_log) - 1), q = tid >> e_log, n_q = BS_THREADS >> e_log;
+  int all = 0, before = 0;
+  for (int r0 = q; r0 < G; r0 += BATCH * n_q) {
+    int c[BATCH];
+#pragma unroll
+    for (int j = 0; j < BATCH; ++j) {
+      const int r = r0 + j * n_q;
+      c[j] = r < G && e < E ? cnt[static_cast<size_t>(r) * E + e] : 0;
+    }
+#pragma unroll
+    for (int j = 0; j < BATCH; ++j) {
+      all += c[j];
+      before += r0 + j * n_q < b ? c[j] : 0;
+    }
+  }
+  p0 = p0 < 0 ? 0 : (p0 > cap ? cap : p0);
+  p1 = p1 < p0 ? p0 : (p1 > cap ? cap : p1);
+  int v = 0, pe = 0;
+  if (p0 + tid < p1) {     // (latency beside the sums)
+    v = pair_to_sorted[p0 + tid];
+    pe = pair_expert[p0 + tid];
+  }
+  for (int o = 1 << e_log; o < kWave; o <<= 1) {
+    all += __shfl_xor(all, o, kWave);
+    before += __shfl_xor(before, o, kWave);
+  }
+  s_all[tid] = all;
+  s_before[tid] = before;
+  __syncthreads();
+  const int stride = max(1 << e_log, kWave);
+  int n = 0, st = 0;
+  if (tid < E)
+    for (int x = tid; x < BS_THREADS; x += stride) {
+      n += s_all[x];
+      st += s_before[x];
+    }
+  int incl = 0;
+  if (tid < REFLEX_MAX_EXPERTS) {
+    incl = wave_inclusive_scan_i32(n, lane);
+    if (lane == 63) s_wave[wv] = incl;
+  }
+  __syncthreads();
+  if (tid < E) {
+    int eoff = 0;
+    for (int x = 0; x < wv; ++x) eoff += s_wave[x];
+    const int base = eoff + incl - n;
+    s_base[tid] = base + st;
+    if (b == 0) {
+      expert_offsets[tid] = base;
+      if (tid == E - 1) expert_offsets[E] = base + n;
+    }
+  }
+  __syncthreads();
+  for (int p = p0 + tid; p < p1; p += BS_THREADS) {
+    if (p != p0 + tid) {
+      v = pair_to_sorted[p];
+      pe = pair_expert[p];
+    }
+    pe = pe < 0 ? 0 : (pe >= E ? E - 1 : pe);
+    int pos = s_base[pe] + (v & 31);
+    pos = pos < 0 ? 0 : (pos >= cap ? cap - 1 : pos);
+    sorted_token[pos] = v >> 5;
+    pair_to_sorted[p] = pos;
+  }
+}
+
 }  // namespace
 
 int launch_count_rule(const float* logits, int n_parts, size_t part_stride, const float* bias,
@@ -857,6 +939,10 @@ bool route_fused_sorts(int T, int E) {
   return static_cast<long>((T + RF_WAVES - 1) / RF_WAVES) * E <= RF_HIST_MAX;
 }
 
+static bool sorts_in_one(int T, int E) {
+  return static_cast<long>((T + RF_WAVES - 1) / RF_WAVES) * E <= BS_ONE_MAX;
+}
+
 bool route_block_sorts(int T, int E) {
   const long n = static_cast<long>((T + RF_WAVES - 1) / RF_WAVES) * E;
   return n > RF_HIST_MAX && n <= BS_MAX_COUNTS;
@@ -871,6 +957,13 @@ int launch_block_sort(const int32_t* pair_offsets, const int32_t* pair_expert, i
                       int32_t* pair_to_sorted, hipStream_t s) {
   if (T <= 0) return REFLEX_OK;
   const int G = (T + RF_WAVES - 1) / RF_WAVES;
+  if (sorts_in_one(T, E)) {
+    int e_log = 0;
+    while ((1 << e_log) < E) ++e_log;
+    hipLaunchKernelGGL(block_sort_kernel, dim3(G), dim3(BS_THREADS), 0, s, pair_offsets, pair_expert,
+                       T, cap, E, e_log, G, hist, expert_offsets, sorted_token, pair_to_sorted);
+    return launch_status();
+  }
   int32_t* tot = hist + static_cast<size_t>(G) * E;
   hipLaunchKernelGGL(block_colscan_kernel, dim3(E), dim3(BS_THREADS), 0, s, hist, G, tot);
   hipLaunchKernelGGL(block_scatter_kernel, dim3(G), dim3(256), 0, s, pair_offsets, pair_expert, T,
@@ -895,7 +988,7 @@ int launch_route_fused(const float* logits, int n_parts, size_t part_stride, con
   }
   hipLaunchKernelGGL(kernel, dim3((T + RF_WAVES - 1) / RF_WAVES), dim3(RF_WAVES * kWave), 0, s, logits,
                      n_parts, part_stride, bias, logits_out, k, k_out, T, E, k_max, norm_topk, pair_offsets,
-                     pair_expert, pair_weight, pairs_out, done, hist, expert_offsets, sorted_token, pair_to_sorted);
+                     pair_expert, pair_weight, pairs_out, done, hist, expert_offsets, sorted_token, pair_to_sorted, sorts_in_one(T, E) ? 1 : 0);
   return launch_status();
 }
 

@@ -196,3 +196,26 @@ def test_counts_beside_the_scores(torch, T, E, B):
         ref = ref + w.router_bias
     got = lay.logits.cpu().numpy()[toks]
     assert (np.abs(got - ref).max(1) <= 1e-4 * np.abs(ref).max(1)).all()
+
+
+@pytest.mark.parametrize("T,E", [(1024, 16), (1025, 16), (16401, 1), (9000, 3), (700, 24), (2705, 96),
+                                 (4096, 64), (4097, 64), (65, 256), (1024, 256), (1040, 256)])
+def test_pair_sort_launches(torch, T, E):
+    # the pair sort inside the route launch up to 1024 (16-token block, expert) counts, in
+    # one launch up to 16384, in two above: both sides of each line, expert counts that
+    # share a wave, straddle two and leave lanes empty
+    from test_gpu_parity import _fused_routing, _fuzz_layer
+    w = make_fuzz_workload(T, T=T, d=128, E=E, f=64, k_max=min(E, 12))
+    lay, st = _fuzz_layer(torch, w)
+    for k in (None, np.random.default_rng(T).integers(0, w.params.k_max + 1, T) * (np.arange(T) % 40 < 25)):
+        lay.forward(to_device(w.h), st, k_in=None if k is None else to_device(k.astype(np.int32)))
+        torch.cuda.synchronize()
+        route = oracle.topk_route(lay.logits.cpu().numpy().astype(np.float64),
+                                  lay.k.cpu().numpy() if k is None else k)
+        ref = oracle.pair_permutation(route.token, route.expert, E)
+        got, P = _fused_routing(torch, lay, w), int(route.offsets[-1])
+        assert np.array_equal(got["pair_offsets"], route.offsets)
+        assert np.array_equal(got["pair_expert"][:P], route.expert)
+        assert np.array_equal(got["expert_offsets"], ref.expert_offsets)
+        assert np.array_equal(got["sorted_token"][:P], ref.sorted_token)
+        assert np.array_equal(got["pair_to_sorted"][:P], ref.pair_to_sorted)
