@@ -144,7 +144,7 @@ __device__ __forceinline__ void store_block(const f32x16_t& g, const f32x16_t& u
 //
 // The main shape is 256 pair rows x 256 weight rows x 64 (K) by 8 waves on
 // v_mfma_f32_32x32x16_bf16 with fp32 accumulators.  Experts with hundreds of rows are bound
-// by the MFMAs, those with few by the weight stream; one tile serves both, because copies and
+// by the MFMAs, those with few by the weight stream; one kernel serves both, because copies and
 // MFMAs of absent rows are skipped and an expert of up to 256 rows then reads its weights
 // once.  (128-row tiles with dedicated copier waves, which launches with fewer than 512 rows
 // per expert at pair capacity used before: LLaDA-MoE shape, up + down GEMM at 6 / 80 / 160 /
@@ -190,8 +190,9 @@ struct Geometry {
   static constexpr int B_OPS = BROWS / TL_ROWS_PER_OP / S::WAVES;
   static constexpr int B_WROWS = BROWS / S::WAVES;                      // weight rows a wave copies
   static constexpr int RING = S::A_SLOTS * A_ELEMS + S::B_SLOTS * B_ELEMS;
-  static constexpr bool STAGE_IN_RING = S::WM * S::WN * ST_ELEMS <= A_ELEMS;
-  static constexpr size_t LDS = 2 * size_t(RING + (STAGE_IN_RING ? 0 : S::WM * S::WN * ST_ELEMS));
+  static constexpr bool STAGE_IN_A = S::WM * S::WN * ST_ELEMS <= A_ELEMS;     // else in a weight slot
+  static constexpr size_t LDS = 2 * size_t(RING);
+  static_assert(S::WM * S::WN * ST_ELEMS <= (STAGE_IN_A ? A_ELEMS : B_ELEMS), "staging fits a slot");
   // Copies that may still be in flight when a K step starts: those issued after its own input
   // rows (A_SLOTS - 1 steps ago) and weights (no later than the rows).
   static constexpr int IN_FLIGHT = (S::B_SLOTS > S::A_SLOTS ? B_OPS : 0) + (S::A_SLOTS - 2) * (A_OPS + B_OPS);
@@ -707,6 +708,12 @@ __global__ __launch_bounds__(Geometry<S>::THREADS) void swiglu_gemm_kernel(
         case 1: k_loop(std::integral_constant<int, 1>{}); break;
         default: k_loop(std::integral_constant<int, 0>{}); break;
       }
+    } else if constexpr (TL_MI == 2) {
+      switch (nb) {
+        case 2: k_loop(std::integral_constant<int, 2>{}); break;
+        case 1: k_loop(std::integral_constant<int, 1>{}); break;
+        default: k_loop(std::integral_constant<int, 0>{}); break;
+      }
     } else {
       static_assert(TL_MI == 1, "instances");
       if (nb == 1)
@@ -714,11 +721,13 @@ __global__ __launch_bounds__(Geometry<S>::THREADS) void swiglu_gemm_kernel(
       else
         k_loop(std::integral_constant<int, 0>{});
     }
-    // every wave has read the tile's last input-row slice: its slot takes the staging
+    // every wave has read the tile's last slices: the input-row slot takes the staging, or the
+    // weight slot where that one is too small
     // (the next tile's first step refills it only after its own barrier)
     lds_barrier();
-    uint16_t* stage = (G::STAGE_IN_RING ? a_ring + ((s + TL_A_SLOTS - 1) % TL_A_SLOTS) * TL_A_ELEMS
-                                        : smem + G::RING) + wave * ST_ELEMS;
+    uint16_t* stage = (G::STAGE_IN_A ? a_ring + ((s + TL_A_SLOTS - 1) % TL_A_SLOTS) * TL_A_ELEMS
+                                     : b_ring + ((s + TL_B_SLOTS - 1) % TL_B_SLOTS) * TL_B_ELEMS) +
+                      wave * ST_ELEMS;
 #pragma unroll
     for (int i = 0; i < TL_MI; ++i) {
       if (i < nb) {
@@ -739,7 +748,8 @@ __global__ __launch_bounds__(Geometry<S>::THREADS) void swiglu_gemm_kernel(
 }
 // The tile shapes (pair rows x weight rows); the rule between them is at launch_gemm.
 using Tall = Shape<4, 2, 4, 8, 2, 3>;       // 256 x 256, 160 KB of LDS, one workgroup per CU
-using Medium = Shape<1, 2, 2, 4, 2, 3>;     // 64 x 128, 64 KB, two per CU
+using Half = Shape<2, 2, 4, 8, 3, 3>;       // 128 x 256, 144 KB, one per CU
+using Medium = Shape<1, 2, 2, 4, 3, 3>;     // 64 x 128, 72 KB, two per CU
 using Narrow = Shape<1, 1, 1, 4, 3, 3>;     // 32 x 64, 36 KB, four per CU
 
 // Persistent workgroups: as many as the LDS admits per CU, rounded up to a multiple of the
@@ -785,8 +795,20 @@ long capacity_tiles(int cap, int E, int sh_rows, int N) {
 // does, and its finer tiles spread over the CUs more evenly: forward of the LLaDA-MoE shape
 // at T = 1 / 5 / 32 60 / 139 / 162 us with 256-row tiles, 47 / 112 / 158 us with 32-row ones,
 // LLaDA2.0-mini shape at T = 8 / 32 148 / 279 against 119 / 252 us; at T = 64 64-row tiles 97
-// against 98 us (skewed).  With more tokens the smaller tiles read an expert's weights more
-// than once (LLaDA-MoE, T = 1024: 191 / 228 / 288 us with 256 / 64 / 32 rows) and pay only
+// against 98 us (skewed).
+//
+// With more tokens the pair capacity decides, the most rows the experts may hold on average
+// (LLaDA-MoE and LLaDA2.0-mini use 0.4 to 0.6 of it).  Up to 192, weights bound the launch: 128-row
+// tiles leave LDS for a third input-row slice, and so a whole K step more for the copies to
+// land; forward with 256- / 128-row tiles: LLaDA-MoE T = 256 / 1024 (48 / 192) 171 / 187
+// against 168 / 184 us, T = 2048 (384, whose experts need two 128-row tiles) 224 against 243;
+// LLaDA2.0-mini T = 777 / 4096 (36 / 192) 342 / 415 against 336 / 417, T = 5000 (234) 444 against
+// 458; skewed T = 1500 / 4096 (70 / 192) 176 / 281 against 155 / 265.  Up to 32, 64-row tiles:
+// few experts hold more, and half as many weight rows per tile spread a skewed load better
+// (T = 128 / 512, 128- against 64-row tiles: skewed 134 / 131 against 118 / 122 us;
+// LLaDA-MoE T = 170 165.5 against 164.4, LLaDA2.0-mini T = 300 331 against 329; past the line
+// skewed T = 1024 145 against 156).  Other launches of smaller tiles read an expert's weights
+// more than once (LLaDA-MoE, T = 1024: 191 / 228 / 288 us with 256 / 64 / 32 rows) and pay only
 // where 256-row tiles would leave half of the CUs without work (8 experts of width 512, d =
 // 256: forward at T = 128 / 512 / 2048 34.8 / 40.3 / 49.7 us with 256-row tiles, 28.6 / 29.9 /
 // 40.5 with 64-row ones; T = 4096, 256 tiles: up GEMM 16.9 against 20.1 us).  The same line
@@ -811,10 +833,13 @@ int launch_gemm(const uint16_t* x, const int32_t* gather, const int32_t* eo, int
     const bool alone = E == 0 && T > Geometry<Medium>::BM;
     const bool few = 2 * capacity_tiles<UP, Tall>(cap, E, sh.rows, N) <= cus;
     if (!alone) {
+      const auto holds = [&](int rows) { return cap <= static_cast<long>(rows) * E; };
       if (T <= Geometry<Narrow>::BM || (few && 4 * capacity_tiles<UP, Medium>(cap, E, sh.rows, N) <= cus))
         launch = &launch_gemm_as<UP, Narrow, false>;
-      else if (T <= Geometry<Medium>::BM || few)
+      else if (T <= Geometry<Medium>::BM || few || holds(32))
         launch = &launch_gemm_as<UP, Medium, false>;
+      else if (holds(192))
+        launch = &launch_gemm_as<UP, Half, false>;
     }
   }
   return launch(x, gather, eo, E, w0, w1, stride, sh, K, N, x_rows, cap, out, s);

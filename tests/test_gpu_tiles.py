@@ -32,15 +32,18 @@ SHAPES = [
     # few 256-row tiles: 32-row and 64-row tiles with many rows an expert
     (300, 3, 256, 64, [500, 0, 33], 10),
     (1200, 5, 640, 320, [512, 511, 1, 0, 257], 10),
-    # 256 x 256 tiles
+    # 256 x 256, 128 x 256 and 64 x 128 tiles, by the pair capacity
     (900, 100, 640, 320, [0, 1, 31, 33, 255, 256, 257, 511, 512, 513, 700], 120),
     (200, 160, 128, 64, [256, 257, 0, 1], 40),    # K loops of 2 and 1 steps
     (200, 256, 256, 128, [300, 0, 255], 30),      # K loops of 4 and 2 steps
+    (100, 140, 640, 320, [0, 1, 31, 32, 33, 63, 64, 65, 96, 97, 127, 128, 129, 192, 193], 50),
 ]
 
 
+# capacity: the pairs + 5, or this many per expert (past 32: 128-row tiles, past 192: 256-row ones)
+@pytest.mark.parametrize("per_expert", [0, 40, 200])
 @pytest.mark.parametrize("case", range(len(SHAPES)))
-def test_tile_shapes(torch, case):
+def test_tile_shapes(torch, case, per_expert):
     from paper_2608_01784_amd import _lib as L
     T, E, d, f, first, most = SHAPES[case]
     rng = np.random.default_rng([case, 41])
@@ -55,10 +58,10 @@ def test_tile_shapes(torch, case):
 
     h, wg, wu = bf16((T, d), 1.0), bf16((E, f, d), d ** -0.5), bf16((E, f, d), d ** -0.5)
     wd = bf16((E, d, f), 0.3 * f ** -0.5)
-    cap = P + 5
+    cap = max(P + 5, per_expert * E)
     y = torch.full((cap, d), float("nan"), dtype=torch.bfloat16, device="cuda")
     ws = torch.empty(L.reflex_swiglu_workspace_size(cap, E, f), dtype=torch.uint8, device="cuda")
-    L.reflex_grouped_swiglu(to_device(h), to_device(np.concatenate([st, np.zeros(5, np.int32)])),
+    L.reflex_grouped_swiglu(to_device(h), to_device(np.concatenate([st, np.zeros(cap - P, np.int32)])),
                             to_device(eo), to_device(wg), to_device(wu), to_device(wd), y, ws)
     torch.cuda.synchronize()
     yb = bf16_bits(y)
@@ -109,7 +112,7 @@ def test_operands_past_32_bit_offsets(torch, which):
 @pytest.mark.parametrize("T,E,kmax,fs", [
     (24, 64, 12, 128),      # rides, 32-row tiles
     (60, 256, 12, 128),     # rides, 64-row tiles
-    (105, 256, 12, 128),    # rides, 256-row tiles
+    (105, 256, 12, 128),    # rides, 64-row tiles past 64 tokens
     (107, 256, 12, 128),    # just past the rule: launches of its own, tiles cut to 128 rows
     (40, 16, 4, 192),       # another width: launches of its own, 64-row tiles
     (2100, 16, 4, 128),     # launches of its own, tiles cut to 128 rows
@@ -159,12 +162,14 @@ def test_few_large_experts(torch, big, rest):
 
     h, wg, wu = bf16((T, d), 1.0), bf16((E, f, d), d ** -0.5), bf16((E, f, d), d ** -0.5)
     wd = bf16((E, d, f), 0.3 * f ** -0.5)
-    y = torch.full((P, d), float("nan"), dtype=torch.bfloat16, device="cuda")
-    ws = torch.empty(L.reflex_swiglu_workspace_size(P, E, f), dtype=torch.uint8, device="cuda")
+    cap = 200 * E        # (256-row tiles)
+    st = np.concatenate([st, np.zeros(cap - P, np.int32)])
+    y = torch.full((cap, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    ws = torch.empty(L.reflex_swiglu_workspace_size(cap, E, f), dtype=torch.uint8, device="cuda")
     L.reflex_grouped_swiglu(to_device(h), to_device(st), to_device(eo), to_device(wg), to_device(wu),
                             to_device(wd), y, ws)
     torch.cuda.synchronize()
-    yb = bf16_bits(y)
+    yb = bf16_bits(y)[:P]
     ref = np.concatenate([oracle.swiglu_expert(oracle.bf16_to_f64(h[st[eo[e]:eo[e + 1]]]),
                                                *(oracle.bf16_to_f64(w[e]) for w in (wg, wu, wd)))
                           for e in np.flatnonzero(counts)])
