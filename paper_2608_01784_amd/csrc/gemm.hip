@@ -337,8 +337,18 @@ __global__ __launch_bounds__(Geometry<S>::THREADS) void swiglu_gemm_kernel(
     const int er1 = lo + 1 < E ? table_at(eo_r, lo + 1) : eo_E;
     t.expert = lo;
     t.n0 = n * BN;
-    t.row0 = er0 + (m << bm_log);
-    t.row_end = min(min(er1, out_rows), t.row0 + (1 << bm_log));
+    // Tiles of one height, in whole 64-row steps (a block for each wm): an expert just over a
+    // multiple of the tile otherwise leaves a tile of few rows, whose K steps take far more
+    // than their share (copies, barriers, fewer MFMAs per LDS read).  LLaDA-MoE, forward at
+    // 272 / 314 / 375 / 544 rows per expert: 354 / 362 / 377 / 543 us full tiles first, 340 /
+    // 323 / 354 / 527 even ones; 448 / 826 rows, which hardly move: 418 / 744, 421 / 742.
+    int height = 1 << bm_log;
+    if constexpr (TL_BM > 64) {
+      const int tiles = (er1 - er0 + height - 1) >> bm_log;
+      if (tiles > 1) height = ((er1 - er0 + tiles - 1) / tiles + 63) & ~63;
+    }
+    t.row0 = er0 + m * height;
+    t.row_end = min(min(er1, out_rows), t.row0 + height);
     if (t.row0 < 0 || t.row0 >= t.row_end) t.row_end = t.row0;   // inconsistent offsets: no rows
     // K rotation: tile (M tile m of expert e, N tile n) walks its K slices starting at
     // slice n mod nk (down) or (n mod 2 + 5 e) mod nk (up).  The tiles sharing an input-row
