@@ -39,8 +39,9 @@ COPY_CAL_BYTES = 1 << 28       # the plain device copy that calibrates the byte 
 # the grouped GEMM's kernels per stage: 128-row tiles, or 256-row tiles for launches
 # whose experts average many rows (the library picks one per launch)
 MALL_FLUSH_BYTES = 512 << 20   # read before each cold step: twice the Infinity Cache
-STAGE_KERNELS = {"gemm_up": ("swiglu_gemm_kernel<true>", "swiglu_gemm_tall_kernel<true>"),
-                 "gemm_down": ("swiglu_gemm_kernel<false>", "swiglu_gemm_tall_kernel<false>")}
+# Kernel names up to the tile shape (the second of each: recordings of earlier builds).
+STAGE_KERNELS = {"gemm_up": ("swiglu_gemm_kernel<true", "swiglu_gemm_tall_kernel<true"),
+                 "gemm_down": ("swiglu_gemm_kernel<false", "swiglu_gemm_tall_kernel<false")}
 
 
 def log(msg):
@@ -179,7 +180,7 @@ def _counter_rows(path):
 
 
 def _per_dispatch_kib(path, counter, kernel=None, per_forward=1):
-    """Mean counter value (KiB) per dispatch of `kernel`; without a kernel name, of the
+    """Mean counter value (KiB) per dispatch of `kernel` (its name up to the tile shape); without a kernel name, of the
     dispatches with the largest reading (the calibration copy).  With `per_forward` = 2
     each forward launches the kernel twice (routed experts and the shared expert, on two
     streams, so either may come first): the dispatches are taken in consecutive pairs and
@@ -190,7 +191,7 @@ def _per_dispatch_kib(path, counter, kernel=None, per_forward=1):
         top = max(v for _, v in vals)
         sel = [v for _, v in vals if v >= 0.5 * top]
     else:
-        mine = [v for n, v in vals if n == kernel]
+        mine = [v for n, v in vals if n.startswith(kernel)]
         if len(mine) % per_forward:
             raise SystemExit(f"{len(mine)} {counter} dispatches of {kernel} in {path}: "
                              f"not {per_forward} per forward")
@@ -219,12 +220,13 @@ def ingest_pmc(workload, layout, fetch_csv, write_csv, copy_fetch_csv, copy_writ
                            "write_kib": round(cw, 1), "fetch_factor": round(k_fetch, 4),
                            "write_factor": round(k_write, 4)}
     digest = kernel_source_digest()
-    for stage, knames in STAGE_KERNELS.items():
-        present = {n for n, c, _ in _counter_rows(fetch_csv) if c == "FETCH_SIZE"}
-        kname = next((k for k in knames if k in present), knames[0])
-        per_fwd = 2 if shared and kname in STAGE_KERNELS[stage][:1] else 1
-        fk, nf = _per_dispatch_kib(fetch_csv, "FETCH_SIZE", kname, per_fwd)
-        wk, nw = _per_dispatch_kib(write_csv, "WRITE_SIZE", kname, per_fwd)
+    for stage, prefixes in STAGE_KERNELS.items():
+        read = [(v, n) for n, c, v in _counter_rows(fetch_csv) if c == "FETCH_SIZE"]
+        prefix = next((p for p in prefixes if any(n.startswith(p) for _, n in read)), prefixes[0])
+        per_fwd = 2 if shared and prefix == prefixes[0] else 1
+        fk, nf = _per_dispatch_kib(fetch_csv, "FETCH_SIZE", prefix, per_fwd)
+        wk, nw = _per_dispatch_kib(write_csv, "WRITE_SIZE", prefix, per_fwd)
+        kname = max(x for x in read if x[1].startswith(prefix))[1]
         ent = {"workload": workload, "expert_weights": layout, "kernel": stage,
                "kernel_name": kname, "source_sha256": digest,
                "fetch_kib_per_dispatch": round(fk, 1), "write_kib_per_dispatch": round(wk, 1),

@@ -559,7 +559,7 @@ static int moe_forward_impl(const reflex_moe_args* a, void* ws, size_t ws_bytes,
   RFX_TRY(mark(2));
   // pair offsets and TopK in one launch (P lives in pair_offsets[T]); for layers with
   // at most RF_HIST_MAX (token block, expert) counts the pairs are also sorted there,
-  // otherwise by the permutation launches.
+  // otherwise by the block-sort or the permutation launches.
   RFX_TRY(launch_route_fused(scores, n_parts, te, part_bias, scores_out, k, a->k_out, T, E, kcap,
                              a->norm_topk, pair_offsets, pair_expert, pair_weight, a->pairs_out,
                              done, route_hist, expert_offsets, sorted_token, pair_to_sorted, s));
