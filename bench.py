@@ -35,11 +35,9 @@ PEAK_HBM_GBS = 8000.0          # MI355X HBM3E
 DEFAULT_WORKLOAD = "lladamoe_stack16_t8192"   # the largest single-GPU workload
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic.json")
 COPY_CAL_BYTES = 1 << 28       # the plain device copy that calibrates the byte counters
-# rocprofv3 kernel names of the stages with a counter-derived traffic figure
-# the grouped GEMM's kernels per stage: 128-row tiles, or 256-row tiles for launches
-# whose experts average many rows (the library picks one per launch)
 MALL_FLUSH_BYTES = 512 << 20   # read before each cold step: twice the Infinity Cache
-# Kernel names up to the tile shape (the second of each: recordings of earlier builds).
+# rocprofv3 kernel names of the stages with a counter-derived traffic figure, up to the tile
+# shape (the second of each: recordings of earlier builds)
 STAGE_KERNELS = {"gemm_up": ("swiglu_gemm_kernel<true", "swiglu_gemm_tall_kernel<true"),
                  "gemm_down": ("swiglu_gemm_kernel<false", "swiglu_gemm_tall_kernel<false")}
 

@@ -376,10 +376,10 @@ int reflex_moe_forward_noalloc(const reflex_moe_args* args, void* stream);
 /*
  * reflex_moe_forward with timing marks, for benchmarks: identical work, plus
  * hipEventRecord(stage_events[i], stream) at each stage boundary:
- *   0 start, 1 router done (for layers with T < 4096 on the REFLEX budget path one
- *   launch computes the counts and the scores as d/256 partial sums, which step 3 adds
- *   with the bias), 2 counts done (budget / rule / uniform fill / reuse),
- *   3 count scan + TopK done, 4 permutation + GEMM tile plan done,
+ *   0 start, 1 router done (mostly as partial sums over slices of d, which step 2's rule or
+ *   step 3 adds with the bias; on the REFLEX budget path the same launch computes the
+ *   counts), 2 counts done (rule / what is left of the above; uniform counts: step 3),
+ *   3 count scan + TopK done (and the pair sort of small layers), 4 permutation done,
  *   5 gate/up GEMM done, 6 down GEMM done, 7 shared expert done (nothing is left to do
  *   there where its rows ride in the two GEMMs: f_shared = f and T * kcap <= 5 E),
  *   8 combine done.
