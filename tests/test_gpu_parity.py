@@ -643,8 +643,8 @@ def _fuzz_ref(w, logits, k):
 
 @pytest.mark.parametrize("T", [4096, 4112])
 def test_fused_route_sort_limit(torch, T):
-    # the fused forward sorts the pairs inside its route launch while (16-token blocks) x
-    # experts <= 16384 (T = 4096, E = 64: exactly the limit, 256 workgroups) and with the
+    # the fused forward sorts the pairs in one launch while (16-token blocks) x experts
+    # <= 16384 (T = 4096, E = 64: exactly the limit, 256 workgroups) and with the two
     # block-sort launches above it (T = 4112)
     w = make_fuzz_workload(120, T=T, d=128, E=64, f=64, k_max=12)
     lay, st = _fuzz_layer(torch, w)
@@ -680,9 +680,9 @@ def _fused_routing(torch, lay, w):
                                   "T65536E16", "T4096E256D2048", "T2000E256D2048"])
 def test_fused_route_and_permutation_bit_exact(torch, case):
     # the fused forward's TopK pair list and permutation against the oracle's TopK and
-    # permutation on the forward's own fp32 scores: sorted inside the route launch for
-    # layers up to 16384 (16-token block, expert) counts (the tiny and LLaDA-MoE layers,
-    # T = 4096 at E = 64), by the block-sort launches above (T = 4112, the 16-layer
+    # permutation on the forward's own fp32 scores: sorted inside the route launch (the
+    # tiny layers) or in one launch for layers up to 16384 (16-token block, expert) counts
+    # (the LLaDA-MoE layer, T = 4096 at E = 64), by the block-sort launches above (T = 4112, the 16-layer
     # stack's T = 8192 at E = 64, a ragged T = 5003 at E = 96, the skewed layer's
     # T = 16384 at E = 256 with up to 16 experts a token, and T = 65536 at E = 16: four
     # 1024-block chunks per expert column).  At d = 2048 the route kernel adds split-K
@@ -718,8 +718,8 @@ def test_fused_route_and_permutation_bit_exact(torch, case):
 
 @pytest.mark.parametrize("T", [700, 4400])
 def test_fused_consecutive_calls_and_no_pairs(torch, T):
-    # the sort's completion counter (the route launch's at T = 700, the block sort's at
-    # T = 4400) is re-armed by every forward: three forwards in a row on one workspace,
+    # the sort (the route launch's at T = 700, whose completion counter, or the block
+    # sort's at T = 4400) is re-armed by every forward: three forwards in a row on one workspace,
     # with caller counts that differ (the last one all zero, P = 0: an all-zero output),
     # each checked against the oracle
     w = make_fuzz_workload(121, T=T, d=256, E=16 if T < 1000 else 64, f=128, k_max=6)
