@@ -9,6 +9,7 @@ kernels.
 """
 from __future__ import annotations
 
+from contextlib import nullcontext
 from dataclasses import dataclass, field
 from typing import Callable, List, Optional
 
@@ -35,7 +36,10 @@ def run_trajectory(layer: MoELayer, h, state: TokenState, confidence: Callable[[
 
     confidence(t) returns the [T] float32 device tensor of forward t's
     confidences.  on_forward(t, state), if given, is called after each layer
-    forward and before the state update (the state still describes forward t)."""
+    forward and before the state update (the state still describes forward t).
+    The forwards and state updates run on `stream` (default: the current one); both
+    callbacks run on the current stream, which is ordered after the forward before them
+    and before the state update after them."""
     import torch
     stats = TrajectoryStats()
     remaining = torch.empty(state.active_block.shape[0], dtype=torch.int32,
@@ -45,6 +49,16 @@ def run_trajectory(layer: MoELayer, h, state: TokenState, confidence: Callable[[
     # reduction launch before), and the next forward's arguments are prepared ahead of it
     # (LLaDA-MoE layer, T = 1024: 307 us a forward before, 280 now).
     host = torch.empty(1 + remaining.shape[0], dtype=torch.int32, pin_memory=True)
+    # The kernels' stream: the results are copied and waited for there.  Where it is not the
+    # current stream, each waits for the other where one reads what the other has made.
+    current = torch.cuda.current_stream()
+    run = current if stream is None else stream
+    apart = run.cuda_stream != current.cuda_stream
+    if apart:
+        if not hasattr(run, "wait_stream"):      # (any object with a stream handle)
+            run = torch.cuda.ExternalStream(run.cuda_stream)
+        run.wait_stream(current)
+        remaining.record_stream(run)
     own_forward = getattr(layer.forward, "__func__", None) is MoELayer.forward
     args = None
     for t in range(max_forwards):
@@ -52,16 +66,23 @@ def run_trajectory(layer: MoELayer, h, state: TokenState, confidence: Callable[[
             layer.forward(h, state, stream=stream)
         else:
             _lib.reflex_moe_forward(args, layer.ws, stream)
+        if apart:
+            current.wait_stream(run)
         if on_forward is not None:
             on_forward(t, state)
         conf_t = confidence(t)
+        if stream is None:
+            run = torch.cuda.current_stream()
+        elif apart:
+            run.wait_stream(current)
         _lib.reflex_advance_state(conf_t, state.block_idx, state.seq_offsets, theta, min_commit,
                                   state.masked, state.hist_len, state.conf_prev1, state.conf_prev2,
                                   state.active_block, remaining, stream=stream)
-        host[:1].copy_(layer.pairs, non_blocking=True)
-        host[1:].copy_(remaining, non_blocking=True)
+        with torch.cuda.stream(run) if apart else nullcontext():
+            host[:1].copy_(layer.pairs, non_blocking=True)
+            host[1:].copy_(remaining, non_blocking=True)
         args = layer.args(h, state) if own_forward else None
-        torch.cuda.current_stream().synchronize()
+        run.synchronize()
         counts = host.tolist()
         stats.forwards += 1
         stats.pairs.append(counts[0])

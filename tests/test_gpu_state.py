@@ -123,3 +123,39 @@ def test_trajectory_matches_oracle(torch, name, min_commit):
     assert n_checked[0] == stats.forwards
     note(f"{name}: {stats.forwards} forwards, {stats.total_pairs} pairs, "
          f"AvgK {stats.total_pairs / (stats.forwards * w.T):.3f}")
+
+
+def test_trajectory_on_another_stream(torch):
+    # forwards and state updates on a stream that is not the current one, and that other work
+    # keeps busy ahead of them; confidences and the callback's reads on the current stream
+    from paper_2608_01784_amd.layer import ExpertWeights, MoELayer, TokenState
+    from paper_2608_01784_amd.trajectory import run_trajectory
+    w = make_workload("tiny_t128_e8")
+    start = generation_start(w)
+    dw = {"w_gate": to_device(w.w_gate()), "w_up": to_device(w.w_up()), "w_down": to_device(w.w_down()),
+          "w_router": to_device(w.w_router()), "router_bias": None}
+    lay = MoELayer(w.T, w.d, ExpertWeights(**dw), w.params)
+    h = to_device(w.h)
+    side = torch.cuda.Stream()
+    busy = torch.randn(4096, 4096, device="cuda")
+    results = []
+    for stream in (None, side):
+        st = TokenState(**{k: to_device(v) for k, v in start.items()})
+        counts = []
+
+        def confidence(t):
+            if stream is not None:
+                with torch.cuda.stream(side):
+                    busy @ busy
+            return to_device(forward_confidence(5, t, w.T)) * 1.0
+
+        stats = run_trajectory(lay, h, st, confidence, THETA, 0, max_forwards=400,
+                               on_forward=lambda t, s: counts.append((lay.k.sum(), s.masked.sum())),
+                               stream=stream)
+        torch.cuda.synchronize()
+        results.append((stats.pairs, stats.masked_left, [[int(x) for x in c] for c in counts], _host(st)))
+    (pairs, left, counts, final), (pairs2, left2, counts2, final2) = results
+    assert pairs == pairs2 == [c[0] for c in counts] and left == left2 and left[-1] == 0
+    assert counts == counts2
+    for name in final:
+        assert np.array_equal(final[name], final2[name]), name
