@@ -49,6 +49,9 @@ def run_trajectory(layer: MoELayer, h, state: TokenState, confidence: Callable[[
     # reduction launch before), and the next forward's arguments are prepared ahead of it
     # (LLaDA-MoE layer, T = 1024: 307 us a forward before, 280 now).
     host = torch.empty(1 + remaining.shape[0], dtype=torch.int32, pin_memory=True)
+    # Few sequences are added up as a list, many as an array (1 / 64 / 1024 sequences: 1.0 / 2.5 /
+    # 16 us as a list, 2.8 / 2.8 / 2.1 as an array; 65536: a forward 0.3 ms longer).
+    array = host.numpy() if remaining.shape[0] > 64 else None
     # The kernels' stream: the results are copied and waited for there.  Where it is not the
     # current stream, each waits for the other where one reads what the other has made.
     current = torch.cuda.current_stream()
@@ -83,10 +86,10 @@ def run_trajectory(layer: MoELayer, h, state: TokenState, confidence: Callable[[
             host[1:].copy_(remaining, non_blocking=True)
         args = layer.args(h, state) if own_forward else None
         run.synchronize()
-        counts = host.tolist()
         stats.forwards += 1
-        stats.pairs.append(counts[0])
-        left = sum(counts[1:])
+        counts = host.tolist() if array is None else array
+        stats.pairs.append(int(counts[0]))
+        left = sum(counts[1:]) if array is None else int(counts[1:].sum())
         stats.masked_left.append(left)
         if left == 0:
             break

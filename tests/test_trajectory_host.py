@@ -109,3 +109,9 @@ def _run(monkeypatch, other, n_seq=3, per_seq=4):
 @pytest.mark.parametrize("other", [False, True])
 def test_results_come_from_the_stream_the_kernels_run_on(monkeypatch, other):
     _run(monkeypatch, other)
+
+
+def test_many_sequences_are_added_up_without_a_python_list(monkeypatch):
+    # (one element at a time, the host would take longer over many sequences than the forward)
+    monkeypatch.setattr(torch.Tensor, "tolist", lambda t: pytest.fail("tolist of the counts"))
+    _run(monkeypatch, False, n_seq=300)
