@@ -107,3 +107,8 @@ class MoELayer:
         args = self.args(h, state, k_in, residual_a, residual_b, out)
         _lib.reflex_moe_forward(args, self.ws, stream)
         return self.out if out is None else out
+
+
+# The forward as written above: a caller that does without the method (because it has made the
+# arguments already) compares with this, so that a wrapped or replaced one is still called.
+PLAIN_FORWARD = MoELayer.forward

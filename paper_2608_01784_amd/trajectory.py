@@ -14,7 +14,7 @@ from dataclasses import dataclass, field
 from typing import Callable, List, Optional
 
 from . import _lib
-from .layer import MoELayer, TokenState
+from .layer import PLAIN_FORWARD, MoELayer, TokenState
 
 
 @dataclass
@@ -62,7 +62,6 @@ def run_trajectory(layer: MoELayer, h, state: TokenState, confidence: Callable[[
             run = torch.cuda.ExternalStream(run.cuda_stream)
         run.wait_stream(current)
         remaining.record_stream(run)
-    own_forward = getattr(layer.forward, "__func__", None) is MoELayer.forward
     args = None
     for t in range(max_forwards):
         if args is None:
@@ -84,7 +83,8 @@ def run_trajectory(layer: MoELayer, h, state: TokenState, confidence: Callable[[
         with torch.cuda.stream(run) if apart else nullcontext():
             host[:1].copy_(layer.pairs, non_blocking=True)
             host[1:].copy_(remaining, non_blocking=True)
-        args = layer.args(h, state) if own_forward else None
+        plain = getattr(layer.forward, "__func__", None) is PLAIN_FORWARD
+        args = layer.args(h, state) if plain else None
         run.synchronize()
         stats.forwards += 1
         counts = host.tolist() if array is None else array

@@ -115,3 +115,31 @@ def test_many_sequences_are_added_up_without_a_python_list(monkeypatch):
     # (one element at a time, the host would take longer over many sequences than the forward)
     monkeypatch.setattr(torch.Tensor, "tolist", lambda t: pytest.fail("tolist of the counts"))
     _run(monkeypatch, False, n_seq=300)
+
+
+def test_a_replaced_forward_is_called_every_time(monkeypatch):
+    # a program may wrap the layer's forward, on the class or on one layer, also during the run
+    from paper_2608_01784_amd.layer import MoELayer
+    Device(monkeypatch)
+    pairs, masked = torch.zeros(1, dtype=torch.int32), torch.ones(4, dtype=torch.uint8)
+    state = SimpleNamespace(block_idx=None, masked=masked, hist_len=None, conf_prev1=None, conf_prev2=None,
+                            seq_offsets=torch.tensor([0, 4]), active_block=torch.zeros(1))
+    layer = MoELayer.__new__(MoELayer)
+    layer.pairs, layer.ws = pairs, None
+    calls = []
+    monkeypatch.setattr(MoELayer, "args", lambda self, *a: None)
+    monkeypatch.setattr(trajectory._lib, "reflex_moe_forward", lambda a, ws, stream=None: calls.append("plain"))
+    confidence = lambda t: torch.arange(4).eq(t).float()      # noqa: E731
+
+    def replace(t, state):
+        if t == 1:
+            layer.forward = lambda h, state, stream=None: calls.append("layer")
+
+    with monkeypatch.context() as m:
+        m.setattr(MoELayer, "forward", lambda self, h, state, stream=None: calls.append("class"))
+        trajectory.run_trajectory(layer, None, state, confidence, 0.9)
+    assert calls == ["class"] * 4
+    calls.clear()
+    masked.fill_(1)
+    trajectory.run_trajectory(layer, None, state, confidence, 0.9, on_forward=replace)
+    assert calls == ["plain"] * 2 + ["layer"] * 2
