@@ -125,9 +125,9 @@ def test_a_replaced_forward_is_called_every_time(monkeypatch):
     state = SimpleNamespace(block_idx=None, masked=masked, hist_len=None, conf_prev1=None, conf_prev2=None,
                             seq_offsets=torch.tensor([0, 4]), active_block=torch.zeros(1))
     layer = MoELayer.__new__(MoELayer)
-    layer.pairs, layer.ws = pairs, None
+    layer.pairs, layer.ws, layer.out = pairs, None, None
     calls = []
-    monkeypatch.setattr(MoELayer, "args", lambda self, *a: None)
+    monkeypatch.setattr(MoELayer, "args", lambda self, *a: "arguments")
     monkeypatch.setattr(trajectory._lib, "reflex_moe_forward", lambda a, ws, stream=None: calls.append("plain"))
     confidence = lambda t: torch.arange(4).eq(t).float()      # noqa: E731
 
