@@ -381,7 +381,7 @@ int reflex_moe_forward_noalloc(const reflex_moe_args* args, void* stream);
  *   counts), 2 counts done (rule / what is left of the above; uniform counts: step 3),
  *   3 count scan + TopK done (and the pair sort of small layers), 4 permutation done,
  *   5 gate/up GEMM done, 6 down GEMM done, 7 shared expert done (nothing is left to do
- *   there where its rows ride in the two GEMMs: f_shared = f and T * kcap <= 5 E),
+ *   there where its rows ride in the two GEMMs: f_shared = f and T * max(kcap, 1) <= 5 E),
  *   8 combine done.
  * stage_events: host array of REFLEX_N_STAGE_EVENTS hipEvent_t handles created by
  * the caller (hipEventCreate); the library only records them.

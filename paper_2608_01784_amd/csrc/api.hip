@@ -196,13 +196,19 @@ struct Layout {
 };
 
 // An always-on expert as wide as the routed ones rides in their two GEMM launches (its rows
-// follow the T * kcap pair rows) where the pairs leave some of the experts empty, i.e. up to
-// five pairs per expert at capacity: its tiles then take the places of the absent ones, and
-// the fork, the join and two launches go (LLaDA2.0-mini shape, forward at T = 1 / 8 / 96: 68 /
-// 130 / 324 us forked, 42 / 118 / 306 us riding; host time of a forward 73 and 28 us).  With
-// every expert busy they would add a round to the grid (T = 200: 330 against 353 us).
+// follow the T * kcap pair rows) up to five pairs per expert at capacity: the fork, the join
+// and two launches go (host time of a forward 73 and 28 us), and its tiles fill in where
+// experts have few rows or none.  Forward forked / riding, us: LLaDA2.0-mini shape T = 1 / 8 /
+// 96 at K_max = 12 68 / 130 / 324 and 42 / 118 / 306, T = 160 at fixed top-8 318 and 301,
+// T = 640 / 1280 at K_max = 1 307 / 342 and 282 / 330.  From there on little is left of it
+// (T = 192 at K_max = 12, 9 pairs: 327 and 318), and a wide layer loses (256 experts of width
+// 1536, d = 4096, K_max = 1, T = 320 / 960 / 1280: 1159 / 1597 / 1668 and 1156 / 1615 / 1693).
+// The bound is on T too (K_max = 0, no pairs): its rows alone set its work then, and
+// in the routed launches it has the tiles of few rows per expert, which read its weights every
+// 64 rows (K_max = 0, mini shape T = 16384: 200 and 236; 8 experts, d = 8192, f = 3072, T = 1800:
+// 355 and 493).
 bool shared_joins(int T, int E, int f, int fs, int kcap) {
-  return fs == f && static_cast<long long>(T) * kcap <= 5LL * E;
+  return fs == f && static_cast<long long>(T) * std::max(kcap, 1) <= 5LL * E;
 }
 
 bool make_layout(int T, int E, int d, int f, int fs, int kcap, Layout& L) {

@@ -265,3 +265,15 @@ def test_product_path_has_no_cpu_fallback():
             if fn.endswith(".py"):
                 src = open(os.path.join(dirpath, fn)).read()
                 assert "oracle" not in src, fn
+
+
+@pytest.mark.parametrize("E,k_max,T,joins", [
+    (64, 11, 29, True), (64, 11, 31, False), (64, 1, 319, True), (64, 1, 321, False),
+    (64, 0, 319, True), (64, 0, 321, False), (256, 0, 16383, False), (8, 0, 4095, False)])
+def test_always_on_expert_joins_the_routed_launches_for_few_rows_only(L, E, k_max, T, joins):
+    # Riding, its activation rows (128 bytes each here) follow the routed ones in one region;
+    # in launches of its own they are a region by themselves, and an odd number of rows, or no
+    # routed row at all, rounds up to 256 bytes in both.  Output rows take 256 bytes either way.
+    d, f = 128, 64
+    extra = L.reflex_workspace_size(T, E, d, f, f, k_max) - L.reflex_workspace_size(T, E, d, f, 0, k_max)
+    assert extra == T * 2 * (d + f) + (-128 if joins else 128)

@@ -143,6 +143,30 @@ def test_always_on_expert(torch, T, E, kmax, fs, no_pairs):
     note("ok")
 
 
+# K_max = 1 and 0 (no routed pair at all): the always-on expert's rows, not the pairs, are what
+# the launch works on; riding up to five tokens per expert, launches of its own above
+@pytest.mark.parametrize("kmax,T", [(1, 80), (1, 81), (0, 1), (0, 80), (0, 81), (0, 2100), (0, 4100)])
+def test_always_on_expert_with_few_or_no_pairs(torch, kmax, T):
+    from paper_2608_01784_amd.layer import ExpertWeights, MoELayer, TokenState
+    w = make_fuzz_workload(600 + T, T=T, d=256, E=16, f=128, f_shared=128, k_max=1)
+    params = w.params.replace(k_min=min(kmax, w.params.k_min), k_max=kmax)
+    shared = w.shared_weights()
+    lay = MoELayer(w.T, w.d, ExpertWeights(
+        w_gate=to_device(w.w_gate()), w_up=to_device(w.w_up()), w_down=to_device(w.w_down()),
+        w_router=to_device(w.w_router()),
+        router_bias=None if w.router_bias is None else to_device(w.router_bias),
+        ws_gate=to_device(shared[0]), ws_up=to_device(shared[1]), ws_down=to_device(shared[2])), params)
+    out = lay.forward(to_device(w.h), TokenState(**state_tensors(w)))
+    torch.cuda.synchronize()
+    k = lay.k.cpu().numpy()
+    assert k.max(initial=0) <= kmax and int(lay.pairs.item()) == k.sum()
+    route = oracle.topk_route(lay.logits.cpu().numpy().astype(np.float64), k)
+    wg, wu, wd = w.w_gate(), w.w_up(), w.w_down()
+    toks = np.unique(np.linspace(0, w.T - 1, 600).astype(int))
+    ref = oracle.moe_layer(w.h, route, lambda e: (wg[e], wu[e], wd[e]), w.E, shared=shared, tokens=toks)
+    layer_tolerance_check(oracle.bf16_to_f64(bf16_bits(out))[toks], ref, f"K_max {kmax}, T={T}")
+
+
 @pytest.mark.parametrize("big,rest", [(257, 3), (1000, 10), (129, 30), (300, 128)])
 def test_few_large_experts(torch, big, rest):
     # 256-row tiles cut to 128 rows where few experts have far more rows than the others
