@@ -37,9 +37,9 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic.json")
 COPY_CAL_BYTES = 1 << 28       # the plain device copy that calibrates the byte counters
 MALL_FLUSH_BYTES = 512 << 20   # read before each cold step: twice the Infinity Cache
 # rocprofv3 kernel names of the stages with a counter-derived traffic figure, up to the tile
-# shape (the second of each: recordings of earlier builds)
-STAGE_KERNELS = {"gemm_up": ("swiglu_gemm_kernel<true", "swiglu_gemm_tall_kernel<true"),
-                 "gemm_down": ("swiglu_gemm_kernel<false", "swiglu_gemm_tall_kernel<false")}
+# shape, which they name next (a recording of a kernel without one is of another build)
+STAGE_KERNELS = {"gemm_up": "swiglu_gemm_kernel<true, Shape<",
+                 "gemm_down": "swiglu_gemm_kernel<false, Shape<"}
 
 
 def log(msg):
@@ -218,10 +218,9 @@ def ingest_pmc(workload, layout, fetch_csv, write_csv, copy_fetch_csv, copy_writ
                            "write_kib": round(cw, 1), "fetch_factor": round(k_fetch, 4),
                            "write_factor": round(k_write, 4)}
     digest = kernel_source_digest()
-    for stage, prefixes in STAGE_KERNELS.items():
+    for stage, prefix in STAGE_KERNELS.items():
         read = [(v, n) for n, c, v in _counter_rows(fetch_csv) if c == "FETCH_SIZE"]
-        prefix = next((p for p in prefixes if any(n.startswith(p) for _, n in read)), prefixes[0])
-        per_fwd = 2 if shared and prefix == prefixes[0] else 1
+        per_fwd = 2 if shared else 1
         fk, nf = _per_dispatch_kib(fetch_csv, "FETCH_SIZE", prefix, per_fwd)
         wk, nw = _per_dispatch_kib(write_csv, "WRITE_SIZE", prefix, per_fwd)
         kname = max(x for x in read if x[1].startswith(prefix))[1]

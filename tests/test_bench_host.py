@@ -21,11 +21,33 @@ def _write_csv(path, rows):
             w.writerow({"Kernel_Name": k, "Counter_Name": c, "Counter_Value": v})
 
 
-@pytest.mark.parametrize("tall", [False, True])
-def test_ingest_pmc_scales_by_copy_calibration(tmp_path, monkeypatch, tall):
-    kind = "swiglu_gemm_tall_kernel" if tall else "swiglu_gemm_kernel"
-    up = f"void rfx::(anonymous namespace)::{kind}<true>(unsigned short const*, int)"
-    dn = f"void rfx::(anonymous namespace)::{kind}<false>(unsigned short const*, int)"
+TALL, HALF, MEDIUM = "Shape<4, 2, 4, 8, 2, 3>", "Shape<2, 2, 4, 8, 3, 3>", "Shape<1, 2, 2, 4, 3, 3>"
+
+
+def _gemm(up, shape):
+    """A GEMM launch's name as the profiler prints it."""
+    ns = "rfx::(anonymous namespace)::"
+    return f"void {ns}swiglu_gemm_kernel<{up}, {ns}{shape}, false>(unsigned short const*, int)"
+
+
+def test_stage_kernels_are_the_built_librarys():
+    # the names that the ingest looks for, shapes among them, are those of the kernels in the library
+    from paper_2608_01784_amd import _lib
+    if not os.path.exists(_lib.LIB_PATH):
+        pytest.fail("libreflex.so is not built (python -m paper_2608_01784_amd.build)")
+    with open(_lib.LIB_PATH, "rb") as fh:
+        blob = fh.read()
+    for up in (1, 0):
+        for shape in (TALL, HALF, MEDIUM):
+            nums = "".join(f"Li{x.strip()}E" for x in shape[6:-1].split(","))
+            assert f"swiglu_gemm_kernelILb{up}ENS0_5ShapeI{nums}EELb0EE".encode() in blob, (up, shape)
+    for up, prefix in (("true", bench.STAGE_KERNELS["gemm_up"]), ("false", bench.STAGE_KERNELS["gemm_down"])):
+        assert _gemm(up, TALL).split("::", 2)[2].replace("rfx::(anonymous namespace)::", "").startswith(prefix)
+
+
+@pytest.mark.parametrize("shape", [TALL, MEDIUM])
+def test_ingest_pmc_scales_by_copy_calibration(tmp_path, monkeypatch, shape):
+    up, dn = _gemm("true", shape), _gemm("false", shape)
     other = "void rfx::(anonymous namespace)::topk_kernel(float const*)"
     fetch, write = tmp_path / "f.csv", tmp_path / "w.csv"
     cfetch, cwrite = tmp_path / "cf.csv", tmp_path / "cw.csv"
@@ -47,7 +69,7 @@ def test_ingest_pmc_scales_by_copy_calibration(tmp_path, monkeypatch, tall):
     assert data["calibration"]["fetch_factor"] == pytest.approx(2.0)
     assert data["calibration"]["write_factor"] == pytest.approx(1.0)
     ent = {e["kernel"]: e for e in data["entries"]}
-    assert ent["gemm_up"]["kernel_name"] == f"{kind}<true>"
+    assert ent["gemm_up"]["kernel_name"] == f"swiglu_gemm_kernel<true, {shape}, false>"
     assert ent["gemm_up"]["dispatches"] == [2, 2]
     assert ent["gemm_up"]["read_bytes"] == 300 * 1024 * 2
     assert ent["gemm_up"]["write_bytes"] == 20 * 1024
@@ -62,14 +84,12 @@ def test_ingest_pmc_scales_by_copy_calibration(tmp_path, monkeypatch, tall):
 
 def test_ingest_pmc_counts_routed_launches_only_with_a_shared_expert(tmp_path, monkeypatch):
     # per forward: the routed up and down GEMMs and the shared expert's dense up and down
-    # on the same kernels, the shared ones on a second stream, so either pair member may
-    # come first; only the routed launch (the larger reading of each pair) counts
-    up = "void rfx::(anonymous namespace)::swiglu_gemm_kernel<true>(int)"
-    dn = "void rfx::(anonymous namespace)::swiglu_gemm_kernel<false>(int)"
+    # on the same kernel in another tile shape, the shared ones on a second stream, so either
+    # pair member may come first; only the routed launch (the larger reading of each pair) counts
     fetch, write = tmp_path / "f.csv", tmp_path / "w.csv"
     frows, wrows = [], []
-    routed = [(up, 1000, 10), (dn, 500, 50)]
-    shared = [(up, 7, 1), (dn, 3, 2)]
+    routed = [(_gemm("true", HALF), 1000, 10), (_gemm("false", HALF), 500, 50)]
+    shared = [(_gemm("true", TALL), 7, 1), (_gemm("false", TALL), 3, 2)]
     for fwd in range(3):
         order = routed + shared if fwd != 1 else [shared[0], routed[0], shared[1], routed[1]]
         for name, f, w in order:
@@ -95,6 +115,7 @@ def test_ingest_pmc_counts_routed_launches_only_with_a_shared_expert(tmp_path, m
     bench.ingest_pmc("wl", "row-major", str(fetch), str(write), str(cf), str(cw), shared=True)
     ent = {e["kernel"]: e for e in json.loads(tf.read_text())["entries"]}
     assert ent["gemm_up"]["dispatches"] == [3, 3]
+    assert ent["gemm_up"]["kernel_name"] == f"swiglu_gemm_kernel<true, {HALF}, false>"
     assert ent["gemm_up"]["read_bytes"] == 1000 * 1024
     assert ent["gemm_up"]["write_bytes"] == 10 * 1024
     assert ent["gemm_down"]["read_bytes"] == 500 * 1024
@@ -106,9 +127,12 @@ def test_ingest_pmc_counts_routed_launches_only_with_a_shared_expert(tmp_path, m
         bench.ingest_pmc("wl", "row-major", str(fetch), str(write), str(cf), str(cw), shared=True)
 
 
-def test_ingest_pmc_missing_kernel_is_an_error(tmp_path, monkeypatch):
+@pytest.mark.parametrize("other", ["topk_kernel", "swiglu_gemm_kernel<true>", "swiglu_gemm_tall_kernel<true>"])
+def test_ingest_pmc_missing_kernel_is_an_error(tmp_path, monkeypatch, other):
+    # (recordings of kernels that are not in the sources whose digest would be stored are as good as none)
     fetch = tmp_path / "f.csv"
-    _write_csv(fetch, [("void rfx::(anonymous namespace)::topk_kernel(float const*)", "FETCH_SIZE", 1)])
+    _write_csv(fetch, [(f"void rfx::(anonymous namespace)::{name}(float const*)", c, 1)
+                       for name in (other, other.replace("true", "false")) for c in ("FETCH_SIZE", "WRITE_SIZE")])
     monkeypatch.setattr(bench, "TRAFFIC_FILE", str(tmp_path / "traffic.json"))
     ck = bench.COPY_CAL_BYTES / 1024.0
     cf = tmp_path / "cf.csv"
