@@ -177,35 +177,36 @@ def _counter_rows(path):
     return [t[1:] for t in rows]
 
 
-def _per_dispatch_kib(path, counter, kernel=None, per_forward=1):
-    """Mean counter value (KiB) per dispatch of `kernel` (its name up to the tile shape); without a kernel name, of the
-    dispatches with the largest reading (the calibration copy).  With `per_forward` = 2
-    each forward launches the kernel twice (routed experts and the shared expert, on two
-    streams, so either may come first): the dispatches are taken in consecutive pairs and
-    the larger reading of each pair is the routed launch (it reads and writes P > T rows
-    against the shared expert's T, and all the routed weights)."""
+def _per_dispatch_kib(path, counter, kernel=None):
+    """Mean counter value (KiB) per routed dispatch of `kernel` (its name up to the tile
+    shape); without a kernel name, of the dispatches with the largest reading (the
+    calibration copy).  A forward launches the kernel once, or twice where a shared expert
+    has launches of its own (on another stream, so either may come first): as often as
+    there are dispatches for each combine dispatch, of which every forward has one.  The
+    larger reading of a forward is the routed launch (it reads and writes P > T rows against
+    the shared expert's T, and all the routed weights)."""
     vals = [(n, v) for n, c, v in _counter_rows(path) if c == counter]
     if kernel is None:
         top = max(v for _, v in vals)
         sel = [v for _, v in vals if v >= 0.5 * top]
     else:
         mine = [v for n, v in vals if n.startswith(kernel)]
-        if len(mine) % per_forward:
+        forwards = sum(n.startswith("combine_kernel") for n, _ in vals)
+        if mine and (forwards == 0 or len(mine) not in (forwards, 2 * forwards)):
             raise SystemExit(f"{len(mine)} {counter} dispatches of {kernel} in {path}: "
-                             f"not {per_forward} per forward")
-        sel = [max(mine[i:i + per_forward]) for i in range(0, len(mine), per_forward)]
+                             f"not one or two for each of {forwards} forwards")
+        per_forward = len(mine) // max(forwards, 1)
+        sel = [max(mine[i:i + per_forward]) for i in range(0, len(mine), per_forward)] if mine else []
     if not sel:
         raise SystemExit(f"no {counter} dispatches of {kernel or 'the copy'} in {path}")
     return sum(sel) / len(sel), len(sel)
 
 
-def ingest_pmc(workload, layout, fetch_csv, write_csv, copy_fetch_csv, copy_write_csv,
-               shared=False):
+def ingest_pmc(workload, layout, fetch_csv, write_csv, copy_fetch_csv, copy_write_csv):
     """Turn two rocprofv3 --pmc runs of the bench (FETCH_SIZE, WRITE_SIZE) and the same two
     counters on a plain copy of COPY_CAL_BYTES into HBM bytes per GEMM launch, stored in
-    the traffic file under the current GEMM source digest.  With a shared expert
-    (`shared`), every forward launches each GEMM kernel twice, for the routed experts and
-    for the shared expert's dense GEMM; only the routed launches are counted."""
+    the traffic file under the current GEMM source digest.  Only the routed launches are
+    counted, not those of a shared expert that has launches of its own."""
     cf, _ = _per_dispatch_kib(copy_fetch_csv, "FETCH_SIZE")
     cw, _ = _per_dispatch_kib(copy_write_csv, "WRITE_SIZE")
     k_fetch = COPY_CAL_BYTES / (cf * 1024.0)      # true read bytes per counted byte
@@ -220,9 +221,8 @@ def ingest_pmc(workload, layout, fetch_csv, write_csv, copy_fetch_csv, copy_writ
     digest = kernel_source_digest()
     for stage, prefix in STAGE_KERNELS.items():
         read = [(v, n) for n, c, v in _counter_rows(fetch_csv) if c == "FETCH_SIZE"]
-        per_fwd = 2 if shared else 1
-        fk, nf = _per_dispatch_kib(fetch_csv, "FETCH_SIZE", prefix, per_fwd)
-        wk, nw = _per_dispatch_kib(write_csv, "WRITE_SIZE", prefix, per_fwd)
+        fk, nf = _per_dispatch_kib(fetch_csv, "FETCH_SIZE", prefix)
+        wk, nw = _per_dispatch_kib(write_csv, "WRITE_SIZE", prefix)
         kname = max(x for x in read if x[1].startswith(prefix))[1]
         ent = {"workload": workload, "expert_weights": layout, "kernel": stage,
                "kernel_name": kname, "source_sha256": digest,
@@ -585,9 +585,7 @@ def main():
     a = ap.parse_args()
     layout = "row-major"
     if a.ingest_pmc:
-        from synth import make_workload
-        ingest_pmc(a.workload, layout, *a.ingest_pmc,
-                   shared=make_workload(a.workload, seed=a.seed).f_shared > 0)
+        ingest_pmc(a.workload, layout, *a.ingest_pmc)
         return
     if a.gpus != 1 or int(os.environ.get("WORLD_SIZE", "1")) != 1:
         print("bench.py measures one GPU only: this build has no multi-GPU path "

@@ -21,6 +21,7 @@ def _write_csv(path, rows):
             w.writerow({"Kernel_Name": k, "Counter_Name": c, "Counter_Value": v})
 
 
+COMBINE = "void rfx::(anonymous namespace)::combine_kernel<16>(unsigned short const*, int const*)"
 TALL, HALF, MEDIUM = "Shape<4, 2, 4, 8, 2, 3>", "Shape<2, 2, 4, 8, 3, 3>", "Shape<1, 2, 2, 4, 3, 3>"
 
 
@@ -53,9 +54,9 @@ def test_ingest_pmc_scales_by_copy_calibration(tmp_path, monkeypatch, shape):
     cfetch, cwrite = tmp_path / "cf.csv", tmp_path / "cw.csv"
     # two dispatches per GEMM: per-dispatch means 300 / 150 KiB read, 20 / 40 KiB written
     _write_csv(fetch, [(up, "FETCH_SIZE", 200), (up, "FETCH_SIZE", 400), (dn, "FETCH_SIZE", 150),
-                       (dn, "FETCH_SIZE", 150), (other, "FETCH_SIZE", 9)])
+                       (dn, "FETCH_SIZE", 150), (other, "FETCH_SIZE", 9)] + [(COMBINE, "FETCH_SIZE", 8)] * 2)
     _write_csv(write, [(up, "WRITE_SIZE", 20), (up, "WRITE_SIZE", 20), (dn, "WRITE_SIZE", 40),
-                       (dn, "WRITE_SIZE", 40)])
+                       (dn, "WRITE_SIZE", 40)] + [(COMBINE, "WRITE_SIZE", 8)] * 2)
     # the copy reads half of what it moves on FETCH_SIZE (factor 2), all of it on WRITE_SIZE;
     # small readings of other kernels are not the copy
     ck = bench.COPY_CAL_BYTES / 1024.0
@@ -82,17 +83,21 @@ def test_ingest_pmc_scales_by_copy_calibration(tmp_path, monkeypatch, shape):
     assert bench.measured_traffic("wl", "row-major", "gemm_up") is None
 
 
-def test_ingest_pmc_counts_routed_launches_only_with_a_shared_expert(tmp_path, monkeypatch):
-    # per forward: the routed up and down GEMMs and the shared expert's dense up and down
-    # on the same kernel in another tile shape, the shared ones on a second stream, so either
-    # pair member may come first; only the routed launch (the larger reading of each pair) counts
+@pytest.mark.parametrize("own", [True, False])
+def test_ingest_pmc_counts_routed_launches_only_with_a_shared_expert(tmp_path, monkeypatch, own):
+    # per forward: the routed up and down GEMMs and, where the shared expert does not ride in
+    # them, its dense up and down on the same kernel in another tile shape, the shared ones on a
+    # second stream, so either pair member may come first; only the routed launch (the larger
+    # reading of each pair) counts, and every forward's reading where there is one
     fetch, write = tmp_path / "f.csv", tmp_path / "w.csv"
     frows, wrows = [], []
     routed = [(_gemm("true", HALF), 1000, 10), (_gemm("false", HALF), 500, 50)]
     shared = [(_gemm("true", TALL), 7, 1), (_gemm("false", TALL), 3, 2)]
     for fwd in range(3):
         order = routed + shared if fwd != 1 else [shared[0], routed[0], shared[1], routed[1]]
-        for name, f, w in order:
+        if not own:
+            order = [(n, f + 300 * (fwd - 1), w) for n, f, w in routed]
+        for name, f, w in order + [(COMBINE, 11, 13)]:
             frows.append((name, "FETCH_SIZE", f))
             wrows.append((name, "WRITE_SIZE", w))
     def dump(path, rows):
@@ -112,7 +117,7 @@ def test_ingest_pmc_counts_routed_launches_only_with_a_shared_expert(tmp_path, m
     _write_csv(cw, [("copyBuffer", "WRITE_SIZE", ck)])
     tf = tmp_path / "traffic.json"
     monkeypatch.setattr(bench, "TRAFFIC_FILE", str(tf))
-    bench.ingest_pmc("wl", "row-major", str(fetch), str(write), str(cf), str(cw), shared=True)
+    bench.ingest_pmc("wl", "row-major", str(fetch), str(write), str(cf), str(cw))
     ent = {e["kernel"]: e for e in json.loads(tf.read_text())["entries"]}
     assert ent["gemm_up"]["dispatches"] == [3, 3]
     assert ent["gemm_up"]["kernel_name"] == f"swiglu_gemm_kernel<true, {HALF}, false>"
@@ -120,11 +125,11 @@ def test_ingest_pmc_counts_routed_launches_only_with_a_shared_expert(tmp_path, m
     assert ent["gemm_up"]["write_bytes"] == 10 * 1024
     assert ent["gemm_down"]["read_bytes"] == 500 * 1024
     assert ent["gemm_down"]["write_bytes"] == 50 * 1024
-    # a launch count that is not two per forward is an error, not a silent mean
-    dump(fetch, frows[:-1])
-    dump(write, wrows[:-1])
+    # a launch count that is not the same for every forward is an error, not a silent mean
+    dump(fetch, frows[1:])
+    dump(write, wrows[1:])
     with pytest.raises(SystemExit):
-        bench.ingest_pmc("wl", "row-major", str(fetch), str(write), str(cf), str(cw), shared=True)
+        bench.ingest_pmc("wl", "row-major", str(fetch), str(write), str(cf), str(cw))
 
 
 @pytest.mark.parametrize("other", ["topk_kernel", "swiglu_gemm_kernel<true>", "swiglu_gemm_tall_kernel<true>"])
