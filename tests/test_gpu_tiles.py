@@ -248,3 +248,36 @@ def test_pair_sort_launches(torch, T, E):
         assert np.array_equal(got["expert_offsets"], ref.expert_offsets)
         assert np.array_equal(got["sorted_token"][:P], ref.sorted_token)
         assert np.array_equal(got["pair_to_sorted"][:P], ref.pair_to_sorted)
+
+
+# finished scores, the small score tiles' K slices (two of 256 columns) and the large tiles' (two)
+@pytest.mark.parametrize("T,d", [(100, 384), (100, 512), (2048, 512)])
+@pytest.mark.parametrize("counts", ["uniform", "topp", "threshold", "budget"])
+def test_forward_without_the_optional_outputs(torch, T, d, counts):
+    # with no buffers for scores, counts and pair count the forward keeps them in its workspace
+    # (a count rule's finished scores then lie over the first K slice's partials): the same
+    # output and routing, bit for bit, as with them
+    from paper_2608_01784_amd import _lib as L
+    from test_gpu_parity import _fused_routing, _fuzz_layer
+    w = make_fuzz_workload(700 + T, T=T, d=d, E=64, f=64, k_max=12)
+    lay, st = _fuzz_layer(torch, w)
+    lay.k_rule, lay.k_threshold = {"topp": (1, 0.2), "threshold": (2, 0.02)}.get(counts, (0, 0.0))
+    if counts == "uniform":
+        lay.uniform_k = lay.kcap = 7
+    h = to_device(w.h)
+    a = lay.args(h, st)
+    got = []
+    for drop in (False, True):
+        if drop:
+            a.k_out = a.pairs_out = a.logits_out = None
+        lay.ws.fill_(0xff)
+        lay.out.fill_(float("nan"))
+        L.reflex_moe_forward(a, lay.ws)
+        torch.cuda.synchronize()
+        routing = _fused_routing(torch, lay, w)
+        P = int(routing["pair_offsets"][-1])
+        assert P == int(lay.pairs.item()) == int(lay.k.sum().item()) > 0
+        got.append((bf16_bits(lay.out), {n: v if n.endswith("offsets") else v[:P] for n, v in routing.items()}))
+    assert np.array_equal(got[0][0], got[1][0])
+    for name in got[0][1]:
+        assert np.array_equal(got[0][1][name].view(np.int32), got[1][1][name].view(np.int32)), name
