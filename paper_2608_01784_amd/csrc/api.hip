@@ -67,7 +67,6 @@ int check_params(const reflex_alloc_params* p) {
   return REFLEX_OK;
 }
 
-// Fused-path workspace carve-up; every region 256-byte aligned.
 // Threshold of a score-derived count rule: p in (0, 1] for Top-p, tau in [0, 1).
 int check_rule(int rule, float threshold) {
   if (!std::isfinite(threshold)) return REFLEX_ERR_PARAM;
@@ -190,6 +189,7 @@ class SideFork {
   bool have_ev_ = false, forked_ = false, joined_ = false;
 };
 
+// Fused-path workspace carve-up; every region 256-byte aligned.
 struct Layout {
   size_t logits, k, done, pair_offsets, pair_expert, pair_weight, expert_offsets, sorted_token,
       pair_to_sorted, perm, route_hist, swiglu, y, shared_act, shared_y, total;

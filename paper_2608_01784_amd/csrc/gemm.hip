@@ -24,7 +24,8 @@
 // reads are conflict-free, while a wave's copy still writes 1 KB (8 whole rows)
 // contiguously.
 //
-// Scheduling: a persistent grid (one workgroup per CU) walks a flattened
+// Scheduling: a persistent grid (as many workgroups as the LDS admits: one per CU of the
+// large tiles, two and four of the small ones) walks a flattened
 // sequence of (tile, K-slice) steps, so prefetching continues across tile
 // boundaries.  Tiles are dealt to the 8 XCDs in contiguous runs (workgroup b
 // runs on XCD b % 8), so one expert's tiles share that XCD's L2.  Within an
@@ -221,7 +222,7 @@ __global__ __launch_bounds__(Geometry<S>::THREADS) void swiglu_gemm_kernel(
   // input rows mostly hit in L2), so they are copied further ahead and the copies of the next
   // weight slices stay in flight across each step's barrier.  The tile tables live in
   // registers, and the epilogue stages its stores in the input-row slot the tile's last K
-  // step has read (in a buffer of its own where that slot is too small).
+  // step has read (in the weight slot it has read where that one is too small).
   using G = Geometry<S>;
   constexpr int TL_BM = G::BM, TL_A_ELEMS = G::A_ELEMS, TL_B_ELEMS = G::B_ELEMS;
   constexpr int TL_A_OPS = G::A_OPS, TL_B_OPS = G::B_OPS, TL_A_SLOTS = S::A_SLOTS, TL_B_SLOTS = S::B_SLOTS;
@@ -418,9 +419,10 @@ __global__ __launch_bounds__(Geometry<S>::THREADS) void swiglu_gemm_kernel(
   auto set_a = [&](const TT& t) {
     const int rows_valid = t.row_end - t.row0;
     // Input-row copy q holds rows ROWS_PER_OP q ..; copies wholly past the expert's last
-    // row are not issued.  The multiply reads whole 32-row blocks, but only up to the
-    // block holding the last row, and every copy with a row of that block is issued, so
-    // no row it reads is skipped (16-layer stack and skewed layer: 1-2 % less GEMM time,
+    // row are not issued.  The multiply reads whole 32-row blocks up to the one holding the
+    // last row, so it may read up to three groups of 8 rows that were not copied: whatever
+    // the slot held before.  Each of them enters only its own row of the product, and rows
+    // past row_end are not stored (16-layer stack and skewed layer: 1-2 % less GEMM time,
     // identical output; traced in one process).
     int n = (rows_valid + TL_ROWS_PER_OP - 1) / TL_ROWS_PER_OP - TL_A_OPS * wave;
     n = n < 0 ? 0 : (n > TL_A_OPS ? TL_A_OPS : n);
@@ -784,7 +786,7 @@ int launch_gemm_as(const uint16_t* x, const int32_t* gather, const int32_t* eo, 
       return REFLEX_ERR_LAUNCH;
     attr_set = true;
   }
-    hipLaunchKernelGGL(kernel, dim3(persistent_grid<S>()), dim3(Geometry<S>::THREADS), lds, s, x,
+  hipLaunchKernelGGL(kernel, dim3(persistent_grid<S>()), dim3(Geometry<S>::THREADS), lds, s, x,
                      gather, eo, E, w0, w1, stride, sh.w0, sh.w1, sh.row0, sh.rows, K, N, x_rows,
                      out_rows, out);
   return launch_status();
@@ -817,7 +819,10 @@ long capacity_tiles(int cap, int E, int sh_rows, int N) {
 // few experts hold more, and half as many weight rows per tile spread a skewed load better
 // (T = 128 / 512, 128- against 64-row tiles: skewed 134 / 131 against 118 / 122 us;
 // LLaDA-MoE T = 170 165.5 against 164.4, LLaDA2.0-mini T = 300 331 against 329; past the line
-// skewed T = 1024 145 against 156).  Other launches of smaller tiles read an expert's weights
+// skewed T = 1024 145 against 156).  Where the smaller tiles just pass a whole number of rounds
+// of the grid they lose, which the host cannot know: skewed, 12 pairs per token, T = 90 / 100 /
+// 110 / 120 95 / 112 / 112 / 117 us with 64-row tiles, 97 / 103 / 108 / 131 with 128-row ones
+// (100 / 106 / 111 / 139 with the former 128-row kernel).  Other launches of smaller tiles read an expert's weights
 // more than once (LLaDA-MoE, T = 1024: 191 / 228 / 288 us with 256 / 64 / 32 rows) and pay only
 // where 256-row tiles would leave half of the CUs without work (8 experts of width 512, d =
 // 256: forward at T = 128 / 512 / 2048 34.8 / 40.3 / 49.7 us with 256-row tiles, 28.6 / 29.9 /
