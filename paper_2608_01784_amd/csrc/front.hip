@@ -34,9 +34,9 @@ __global__ __launch_bounds__(RS_THREADS) void front_kernel(
 // 128 x 64 tiles of launch_router, which re-read a quarter of the bytes, are faster
 // (stage times, E = 256: T = 512 / 1024 / 2048 / 3000 19.6 / 25.9 / 43.0 / 54.7 us here and
 // 15.3 / 20.7 / 22.7 / 26.1 there; E = 64: T = 1024 / 2048 / 3000 17.8 / 21.2 / 25.1 and 16.9 /
-// 16.8 / 18.3).
+// 16.8 / 18.3; d = 2048), given that their K range splits into enough slices (router_slices).
 bool front_fits(int T, int d, int E) {
-  return static_cast<long>(T) * E < (1L << 17) && T < 4096 && d % RS_KS == 0;
+  return T < 4096 && d % RS_KS == 0 && router_slices(T, d, E) == 1;
 }
 
 int front_slices(int d) { return d / RS_KS; }

@@ -201,13 +201,19 @@ static long big_tiles(int T, int E) {
 // 64-expert LDS-staged tiles re-read neither operand much (h once per 64 experts, W_r
 // once per 128 tokens), so where they are too few to fill the GPU the K range is split
 // instead of shrinking the tiles: up to ~512 workgroups (two fit a CU), slices of at
-// least 256 columns.
+// least 256 columns.  Below T = 4096 the front launch's tiles are there too, and keep the
+// scores where the split leaves these fewer than 64 workgroups, which is wherever d has an
+// odd number of 256-column slices (router stage, E = 256, T = 3000, front against these tiles
+// unsplit: d = 768 / 1280 / 2304 / 2816 23 / 38 / 63 / 68 and 37 / 60 / 103 / 122 us) and few
+// tiles with two slices (32 workgroups, E = 256, T = 512: d = 512 / 1536 / 2560 / 3584 9 / 16 / 19 /
+// 24 and 16 / 22 / 27 / 38 us; from 64 on, E = 256, T = 1024: 15 / 23 / 33 / 38 and 16 / 21 / 28 / 39).
 int router_slices(int T, int d, int E) {
-  if ((T < 4096 && static_cast<long>(T) * E < (1L << 17)) || d % RB_BK != 0) return 1;
+  const bool beside_front = T < 4096;
+  if ((beside_front && static_cast<long>(T) * E < (1L << 17)) || d % RB_BK != 0) return 1;
   const long tiles = big_tiles(T, E);
   int ns = 1;
   while (tiles * ns * 2 <= 512 && d % (2 * ns * 256) == 0) ns *= 2;
-  return ns;
+  return beside_front && tiles * ns < 64 ? 1 : ns;
 }
 
 bool router_takes_counts(int T, int d, int E, int B) {

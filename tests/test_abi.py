@@ -277,3 +277,15 @@ def test_always_on_expert_joins_the_routed_launches_for_few_rows_only(L, E, k_ma
     d, f = 128, 64
     extra = L.reflex_workspace_size(T, E, d, f, f, k_max) - L.reflex_workspace_size(T, E, d, f, 0, k_max)
     assert extra == T * 2 * (d + f) + (-128 if joins else 128)
+
+
+@pytest.mark.parametrize("E,T,d,slices", [
+    (256, 3000, 1280, 5), (256, 3000, 768, 3), (64, 4000, 2816, 11), (256, 512, 1536, 6),   # 256 columns each
+    (256, 512, 2048, 8), (256, 1024, 1536, 2), (64, 2048, 3072, 4),                         # large tiles' slices
+    (256, 512, 1152, 1)])                                                                   # no slices
+def test_scores_are_split_over_k_into_enough_slices(L, E, T, d, slices):
+    # Partial scores take T * E words a slice of the workspace: below T = 4096 the large score
+    # tiles only where their slices fill the GPU, else the small tiles with 256 columns a slice.
+    # (Without pairs nothing else in the workspace depends on d; 1408 is not a multiple of 256.)
+    words = (L.reflex_workspace_size(T, E, d, 64, 0, 0) - L.reflex_workspace_size(T, E, 1408, 64, 0, 0)) // 4
+    assert words == T * E * (slices - 1)

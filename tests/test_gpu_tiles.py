@@ -200,14 +200,16 @@ def test_few_large_experts(torch, big, rest):
     layer_tolerance_check(oracle.bf16_to_f64(yb), ref, f"experts of {big} and {rest} rows")
 
 
-@pytest.mark.parametrize("T,E,B", [(2048, 64, 1), (512, 256, 300), (520, 256, 2), (16384, 256, 1000),
-                                   (4100, 64, 5)])
-def test_counts_beside_the_scores(torch, T, E, B):
+@pytest.mark.parametrize("T,E,B,d", [(2048, 64, 1, 1024), (512, 256, 300, 1024), (520, 256, 2, 1024),
+                                     (16384, 256, 1000, 128), (4100, 64, 5, 512),
+                                     # the small tiles' launch past 2^17 scores (an odd number of slices)
+                                     (2100, 64, 3, 768), (513, 256, 300, 1280), (512, 256, 2, 512)])
+def test_counts_beside_the_scores(torch, T, E, B, d):
     # the launch of large score tiles computes the counts of B sequences in its first
     # workgroups: more sequences than tiles, empty sequences, one sequence of several slices
     from paper_2608_01784_amd.layer import ExpertWeights, MoELayer, TokenState
     from gpu_common import oracle_budget
-    w = make_fuzz_workload(400 + B, T=T, d=512 if T < 16384 else 128, E=E, f=64, k_max=8)
+    w = make_fuzz_workload(400 + B, T=T, d=d, E=E, f=64, k_max=8)
     rng = np.random.default_rng(B)
     cuts = np.sort(rng.integers(0, T + 1, B - 1)) if B > 1 else np.zeros(0, int)
     w.seq_offsets = np.concatenate([[0], cuts, [T]]).astype(np.int32)
@@ -250,8 +252,8 @@ def test_pair_sort_launches(torch, T, E):
         assert np.array_equal(got["pair_to_sorted"][:P], ref.pair_to_sorted)
 
 
-# finished scores, the small score tiles' K slices (two of 256 columns) and the large tiles' (two)
-@pytest.mark.parametrize("T,d", [(100, 384), (100, 512), (2048, 512)])
+# finished scores, the small score tiles' K slices (two of 256 columns) and the large tiles' (four)
+@pytest.mark.parametrize("T,d", [(100, 384), (100, 512), (2048, 1024)])
 @pytest.mark.parametrize("counts", ["uniform", "topp", "threshold", "budget"])
 def test_forward_without_the_optional_outputs(torch, T, d, counts):
     # with no buffers for scores, counts and pair count the forward keeps them in its workspace
