@@ -261,7 +261,9 @@ __global__ __launch_bounds__(Geometry<S>::THREADS) void swiglu_gemm_kernel(
     // always-on expert by itself: up to 4096 rows, to have more tiles beside the routing
     // (LLaDA2.0-mini, T = 4096: forward 422 us uncut, 415 cut; T = 8192: 508 and 541), while
     // the cut tiles still run in one round (d = 2176, 8 experts, always-on width 3456: T = 1500 /
-    // 2083 / 4000 162 / 194 / 338 us cut, 140 / 174 / 255 uncut).
+    // 2083 / 4000 162 / 194 / 338 us cut, 140 / 174 / 255 uncut); past 4096 rows where the whole
+    // tiles take an eighth of the CUs or less, the down GEMM of a narrow layer (d = 128, width 3776,
+    // T = 4874: 133 us uncut, 112 cut).
     auto prefix = [&]() {
       m_total = 0;
 #pragma unroll
@@ -291,8 +293,8 @@ __global__ __launch_bounds__(Geometry<S>::THREADS) void swiglu_gemm_kernel(
           prefix();
         }
       }
-      if (E == 0 && sh_rows <= 4096 && 2 * ((sh_rows + 255) >> 8) * n_tiles <= static_cast<int>(gridDim.x))
-        bm_log = 7;
+      const int whole = ((sh_rows + 255) >> 8) * n_tiles;
+      if (E == 0 && (sh_rows <= 4096 ? 2 : 8) * whole <= static_cast<int>(gridDim.x)) bm_log = 7;
     }
     __syncthreads();     // all scratch reads done before the first copies land
   }

@@ -116,8 +116,9 @@ def test_operands_past_32_bit_offsets(torch, which):
     (107, 256, 12, 128),    # just past the rule: launches of its own, tiles cut to 128 rows
     (40, 16, 4, 192),       # another width: launches of its own, 64-row tiles
     (2100, 16, 4, 128),     # launches of its own, tiles cut to 128 rows
-    (4100, 16, 4, 128),     # launches of its own, 256-row tiles
+    (4100, 16, 4, 128),     # launches of its own, past 4096 rows, still cut
     (600, 16, 4, 5504),     # up: 129 tiles if not cut, 256-row tiles; down: one N tile, cut
+    (8400, 8, 2, 192),      # past an eighth of 256 CUs: 256-row tiles (4100 rows: cut)
 ])
 @pytest.mark.parametrize("no_pairs", [False, True])
 def test_always_on_expert(torch, T, E, kmax, fs, no_pairs):
