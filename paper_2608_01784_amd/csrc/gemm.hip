@@ -831,7 +831,11 @@ long capacity_tiles(int cap, int E, int sh_rows, int N) {
 // more than once (LLaDA-MoE, T = 1024: 191 / 228 / 288 us with 256 / 64 / 32 rows) and pay only
 // where 256-row tiles would leave half of the CUs without work (8 experts of width 512, d =
 // 256: forward at T = 128 / 512 / 2048 34.8 / 40.3 / 49.7 us with 256-row tiles, 28.6 / 29.9 /
-// 40.5 with 64-row ones; T = 4096, 256 tiles: up GEMM 16.9 against 20.1 us).  The same line
+// 40.5 with 64-row ones; T = 4096, 256 tiles: up GEMM 16.9 against 20.1 us).  Weights of more than
+// 8 MB do not stay in an XCD's L2 for the next tile to read: there only while the 64-row tiles
+// run in one round at capacity, else 128-row ones (8 experts of width 1792, d = 3840, top-8, T =
+// 193: forward 179 us with 64-row tiles, 119 with 128-row ones; experts that fill less of the
+// capacity lose by it, d = 2048, width 1024, K_max 4, T = 1000: 57 and 66).  The same line
 // one shape down: 64-row tiles for a quarter of the CUs or fewer (T = 128: 28.6 against 27.9
 // us with 32-row tiles; down GEMM at T = 512: 10.3 against 9.2 us; up GEMM there, 256 tiles:
 // 9.4 against 11.1 us).
@@ -854,11 +858,13 @@ int launch_gemm(const uint16_t* x, const int32_t* gather, const int32_t* eo, int
     const bool few = 2 * capacity_tiles<UP, Tall>(cap, E, sh.rows, N) <= cus;
     if (!alone) {
       const auto holds = [&](int rows) { return cap <= static_cast<long>(rows) * E; };
-      if (T <= Geometry<Narrow>::BM || (few && 4 * capacity_tiles<UP, Medium>(cap, E, sh.rows, N) <= cus))
+      const long medium = capacity_tiles<UP, Medium>(cap, E, sh.rows, N);
+      const bool stay = static_cast<size_t>(E) * N * K <= (size_t(1) << 22);
+      if (T <= Geometry<Narrow>::BM || (few && 4 * medium <= cus))
         launch = &launch_gemm_as<UP, Narrow, false>;
-      else if (T <= Geometry<Medium>::BM || few || holds(32))
+      else if (T <= Geometry<Medium>::BM || (few && (stay || medium <= 2 * cus)) || holds(32))
         launch = &launch_gemm_as<UP, Medium, false>;
-      else if (holds(192))
+      else if (few || holds(192))
         launch = &launch_gemm_as<UP, Half, false>;
     }
   }

@@ -4,6 +4,8 @@ the copy lookahead, operands beyond 32-bit byte offsets.  Every row against the 
 definition, with the layer's bar (bf16 rounding of activation and output)."""
 from __future__ import annotations
 
+import re
+
 import numpy as np
 import pytest
 
@@ -37,6 +39,8 @@ SHAPES = [
     (200, 160, 128, 64, [256, 257, 0, 1], 40),    # K loops of 2 and 1 steps
     (200, 256, 256, 128, [300, 0, 255], 30),      # K loops of 4 and 2 steps
     (100, 140, 640, 320, [0, 1, 31, 32, 33, 63, 64, 65, 96, 97, 127, 128, 129, 192, 193], 50),
+    # few tiles, weights past 8 MB: 128-row tiles from the pair capacity alone (400 pairs an expert)
+    (500, 8, 768, 832, [400, 0, 1, 129, 257, 128], 400),
 ]
 
 
@@ -73,6 +77,42 @@ def test_tile_shapes(torch, case, per_expert):
         got.append(oracle.bf16_to_f64(yb[rows]))
     layer_tolerance_check(np.concatenate(got), np.concatenate(ref), f"T={T} E={E} d={d} f={f} P={P}")
     assert np.isnan(oracle.bf16_to_f64(yb[P:])).all()      # rows past P untouched
+
+
+# T, experts, d, f, pair capacity: pair rows of the up and the down GEMM's tiles
+@pytest.mark.parametrize("T,E,d,f,cap,up,down", [
+    (32, 40, 256, 128, 1280, 32, 32),               # few tokens
+    (64, 64, 512, 1024, 8192, 64, 64),
+    (300, 160, 512, 512, 160 * 32, 64, 64),         # few pairs an expert
+    (300, 160, 512, 512, 160 * 32 + 1, 128, 128),   # up to 192, past them
+    (300, 160, 512, 512, 160 * 192 + 1, 256, 256),
+    (193, 8, 256, 512, 1544, 64, 32),               # few tiles: weights that stay in L2 (2 MB)
+    (2048, 8, 256, 512, 8192, 64, 64),
+    (193, 8, 1024, 1024, 1544, 64, 64),             # 16 MB: 64-row tiles while they run in one round
+    (257, 8, 1024, 1024, 2056, 128, 64),            # up: 8 x 5 x 16 tiles on 512 places
+])
+def test_tile_shape_of_a_launch(torch, T, E, d, f, cap, up, down):
+    # the rule that picks the tile shape, by the names of the kernels that a call launches
+    from torch.profiler import ProfilerActivity, profile
+    from paper_2608_01784_amd import _lib as L
+
+    def zeros(*shape, dtype=torch.bfloat16):
+        return torch.zeros(shape, dtype=dtype, device="cuda")
+
+    args = (zeros(T, d), zeros(cap, dtype=torch.int32), zeros(E + 1, dtype=torch.int32), zeros(E, f, d),
+            zeros(E, f, d), zeros(E, d, f), zeros(cap, d),
+            zeros(L.reflex_swiglu_workspace_size(cap, E, f), dtype=torch.uint8))
+    L.reflex_grouped_swiglu(*args)
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        L.reflex_grouped_swiglu(*args)
+        torch.cuda.synchronize()
+    rows = {}
+    for e in prof.events():
+        m = re.search(r"swiglu_gemm_kernel<(true|false), .*Shape<(\d+), (\d+),", e.name)
+        if m:
+            rows[m[1]] = 32 * int(m[2]) * int(m[3])
+    assert rows == {"true": up, "false": down}
 
 
 @pytest.mark.parametrize("which", ["up", "down"])
